@@ -270,15 +270,17 @@ typedef struct {
                               twice (residual replacement; the passes' iterations count in the stats) */
     int32_t mode;          /* shell_pcg_mode_t */
     int32_t chunk;         /* PCG iterations launched between host convergence checks; 0 = default */
-    int32_t pcg_workgroups; /* work-groups of each PCG kernel (each takes consecutive 512-row groups),
-                               0..1024; 0 = default (512: two per CU).  Batches use the first entry's value */
+    int32_t pcg_workgroups; /* 0 = default: a solve is one launch of resident work-groups where the mesh allows it,
+                               else a chain of kernels of 512 work-groups; 1..1024: the chain, with this many
+                               work-groups per kernel (each takes consecutive 512-row groups).  Batches use
+                               the first entry's value */
     int32_t flags;         /* 0 or SHELL_STEP_NO_GRAPHS; batches use the first entry's value */
     const int32_t* replay_counts; /* host [max_newton][3], REPLAY only: exact PCG iterations */
 } shell_step_params_t;
 
-/* PCG iterations are launched as captured HIP graphs of 8..128 iterations (replayed from a cache
- * keyed by the launch shape); this flag launches every kernel directly instead.  Graphs are not used
- * while in-step sampling is on. */
+/* The PCG iterations of a chain of kernels are launched as captured HIP graphs of 8..128 iterations (replayed
+ * from a cache keyed by the launch shape); this flag launches every kernel directly instead.  Graphs are
+ * not used while in-step sampling is on. */
 #define SHELL_STEP_NO_GRAPHS 1
 
 typedef struct {
@@ -399,7 +401,9 @@ typedef struct {
                              bending and membrane tiles together */
     double spmv_ms;       /* PCG direction update p = D^-1 r + beta p and product q = (M + dt^2 K_s) p
                              (with the membrane: + dt^2 K_m p, coordinates coupled) */
-    double update_ms;     /* PCG y/r update with its dot products */
+    double update_ms;     /* PCG y/r update with its dot products.  Where a solve is one launch, both are phases
+                             of its iterations by the kernel's own clock: the first until p.q is known, the
+                             second until r.z has been sent */
     double direction_ms;  /* always 0: the direction update is part of the product kernel */
     int32_t reps;
     int32_t reserved;
@@ -411,8 +415,9 @@ shell_status_t shell_sim_time_kernels(shell_sim_t sim, double dt, int32_t reps, 
 /*
  * Sampled kernel timing inside real steps.  With sampling on, every step of the batch (or simulation)
  * records HIP events on its stream around every force launch set and around every `every`-th PCG
- * iteration's two kernels, and sums the sampled durations per phase; the events are read at the
- * step's existing host synchronisations, so the step's launches and results are unchanged.
+ * iteration's two kernels (or, where a solve is one launch, its first member notes the two phases of every
+ * `every`-th iteration by the wall clock), and sums the sampled durations per phase; they are read at the
+ * step's existing host synchronisations, so the step's results are unchanged.
  *   shell_batch_profile(b, every)  every > 0: start sampling and clear the sums; every == 0: stop.
  *   shell_batch_profile_read(b, out)  copy the sums (sampling continues).
  * The simulation forms act on a simulation's own one-member batch.

@@ -457,6 +457,8 @@ shell_status_t shell_assemble_constant_hessian(shell_stencils_t st, shell_stream
         if (st->precision == SHELL_PREC_MIXED) h->valf.alloc(size_t(P.nslots));
         h->kdiag.alloc(size_t(st->nv));
         launch_assemble(*h, s);
+        // with the membrane the step has a solver of its own, and the direct product was asked for
+        if ((st->cfg_flags & (SHELL_FLAG_DIRECT_PRODUCT | SHELL_FLAG_MEMBRANE)) == 0) build_team(*h, s);
         *out = h.release();
         return SHELL_OK;
     });
@@ -888,12 +890,17 @@ shell_status_t shell_sim_device_bytes(shell_sim_t sim, int64_t* stencil_bytes, i
             a += int64_t(v);
         for (size_t v : {h.scol.bytes(), h.width.bytes(), h.sptr.bytes(), h.rowlen.bytes(), h.val.bytes(),
                          h.valf.bytes(), h.kdiag.bytes(), h.pin.bytes(), h.qout.bytes(), h.gptr.bytes(),
-                         h.gcols.bytes(), h.lcol.bytes()})
+                         h.gcols.bytes(), h.lcol.bytes(), h.tptr.bytes(), h.twid.bytes(), h.tval.bytes(),
+                         h.tvalf.bytes()})
             b += int64_t(v);
+        {
+            std::lock_guard<std::mutex> lk(sim->h->parts_mutex);
+            for (const auto& p : h.parts) b += int64_t(p->bytes());
+        }
         for (size_t v : {sim->x.bytes(), sim->v.bytes(), sim->xt.bytes(), sim->xhat.bytes(), sim->g.bytes(),
                          sim->mass.bytes(), sim->y.bytes(), sim->r.bytes(), sim->f.bytes(), sim->dinv.bytes(), sim->mq.bytes(),
                          sim->pinned.bytes(), sim->p.bytes(), sim->p2.bytes(), sim->z.bytes(), sim->q.bytes(),
-                         sim->bins.bytes(), sim->partials.bytes(), sim->y64.bytes(), sim->rq.bytes(),
+                         sim->bins.bytes(), sim->slots.bytes(), sim->partials.bytes(), sim->y64.bytes(), sim->rq.bytes(),
                          sim->zmass.bytes(), sim->fext.bytes(), sim->ustep.bytes()})
             c += int64_t(v);
         if (sim->ms) c += int64_t(sim->ms->bytes());

@@ -5,6 +5,8 @@
 // Hessian is G (x) I3, so only the scalar K_s is stored.  Storage is SELL-64: slice s holds rows
 // 64s..64s+63 and entry q of row i sits at sptr[s] + 64 q + (i mod 64), so the 64 lanes of a wave read
 // 64 consecutive values and column ids per step (fully coalesced), one row per lane, no reduction.
+#include <algorithm>
+
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
@@ -85,6 +87,63 @@ __global__ void to_float(const double* __restrict__ a, float* __restrict__ b, lo
     if (i < n) b[i] = float(a[i]);
 }
 
+// The off-diagonal entries of row i in the pairs of a team solve: the value pairs (float64 or float32).
+template <typename MR>
+__global__ void team_values(const int32_t* __restrict__ scol, const double* __restrict__ val,
+                            const int64_t* __restrict__ sptr, const int32_t* __restrict__ rowlen, long nv,
+                            const int64_t* __restrict__ tptr, const int32_t* __restrict__ twid,
+                            MR* __restrict__ tval) {
+    const long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
+    if (i >= 64 * ((nv + 63) / 64)) return;
+    const long s = i >> 6, s0 = sptr[s] + (i & 63), t0 = tptr[s] + (i & 63);
+    const int n = i < nv ? rowlen[i] : 0;
+    int o = 0;
+    for (int k = 0; k < n; ++k) {
+        if (scol[s0 + 64L * k] == i) continue;
+        tval[2 * (t0 + 64L * (o >> 1)) + (o & 1)] = MR(val[s0 + 64L * k]);
+        ++o;
+    }
+    for (; o < 2 * twid[s]; ++o) tval[2 * (t0 + 64L * (o >> 1)) + (o & 1)] = MR(0);
+}
+
+// Their columns as ids of a member of R rows: an own row's offset, or R + the halo column's index.
+__global__ void team_columns(const int32_t* __restrict__ scol, const int64_t* __restrict__ sptr,
+                             const int32_t* __restrict__ rowlen, long nv, const int64_t* __restrict__ tptr,
+                             const int32_t* __restrict__ twid, int R, const int32_t* __restrict__ hptr,
+                             const int32_t* __restrict__ hcols, uint32_t* __restrict__ tcol) {
+    const long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
+    if (i >= 64 * ((nv + 63) / 64)) return;
+    const long s = i >> 6, s0 = sptr[s] + (i & 63), t0 = tptr[s] + (i & 63);
+    const long m = i / R, base = m * R;
+    const int n = i < nv ? rowlen[i] : 0;
+    const uint32_t self = uint32_t(i - base);
+    int o = 0;
+    uint32_t pair = 0;
+    auto put = [&](uint32_t id) {
+        pair = (o & 1) ? pair | (id << 16) : id;
+        if (o & 1) tcol[t0 + 64L * (o >> 1)] = pair;
+        ++o;
+    };
+    for (int k = 0; k < n; ++k) {
+        const int c = scol[s0 + 64L * k];
+        if (c == i) continue;
+        if (c >= base && c < base + R) {
+            put(uint32_t(c - base));
+        } else {
+            int lo = hptr[m], hi = hptr[m + 1] - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (hcols[mid] < c)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
+            put(uint32_t(R + lo - hptr[m]));
+        }
+    }
+    while (o < 2 * twid[s]) put(self);
+}
+
 // q = diag(mass) p + dt2 K_s p over 3 columns (caller order handled by the host wrapper)
 __global__ void apply_sell(const int32_t* __restrict__ scol, const double* __restrict__ val,
                            const int64_t* __restrict__ sptr, const int32_t* __restrict__ width,
@@ -153,6 +212,124 @@ void launch_assemble(shell_hessian_s& h, hipStream_t s) {
         SHELL_HIP(hipGetLastError());
     }
     SHELL_HIP(hipStreamSynchronize(s));  // temporaries are released on return
+}
+
+// Rows per member of a simulation on its own.  One member up to 1024 rows (no meetings: 6.8 us per iteration
+// against 7.5 with two members of 512); then few rows each, since an iteration's product is a chain of
+// latencies that grows with a member's rows: 256 while one wave can read all members' sums (4225 rows: 7.6 us
+// against 8.5 with 512 and 10.5 with 1024), 512 up to as many members as compute units (32761 rows: 9.5 us
+// against 10.4 with 256), beyond that whatever keeps one member per unit.
+static int64_t team_rows(int64_t nv) {
+    int dev = 0, cus = 0;
+    SHELL_HIP(hipGetDevice(&dev));
+    SHELL_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    auto whole = [](int64_t n) { return (n + 63) / 64 * 64; };
+    if (nv <= 1024) return whole(nv);
+    if (nv <= 64 * 256) return 256;
+    return std::max<int64_t>(512, whole((nv + cus - 1) / cus));
+}
+
+// The part with members of R rows, or null where it does not fit: each member's halo (the columns of its rows
+// that are other members' rows, ascending), the rows that others read, and the pairs' local columns.
+static std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, hipStream_t s) {
+    const SellPattern& P = h.pat;
+    const int64_t nv = P.nv, members = (nv + R - 1) / R;
+    if (R > kTeamMaxRows) return nullptr;
+    std::vector<std::vector<int32_t>> halo(static_cast<size_t>(members));
+    host_parallel_for(members, [&](int64_t a, int64_t b) {
+        for (int64_t m = a; m < b; ++m) {
+            auto& v = halo[size_t(m)];
+            const int64_t lo = m * R, hi = std::min(nv, lo + R);
+            for (int64_t e = P.rowptr[size_t(lo)]; e < P.rowptr[size_t(hi)]; ++e)
+                if (P.col[size_t(e)] < lo || P.col[size_t(e)] >= hi) v.push_back(P.col[size_t(e)]);
+            std::sort(v.begin(), v.end());
+            v.erase(std::unique(v.begin(), v.end()), v.end());
+        }
+    });
+    auto part = std::make_unique<TeamPart>();
+    part->rows = int32_t(R);
+    part->members = int32_t(members);
+    std::vector<int32_t> hptr(size_t(members + 1), 0), hcols;
+    std::vector<uint8_t> send(size_t(nv), 0);
+    for (int64_t m = 0; m < members; ++m) {
+        const auto& v = halo[size_t(m)];
+        part->max_halo = std::max(part->max_halo, int32_t(v.size()));
+        hcols.insert(hcols.end(), v.begin(), v.end());
+        hptr[size_t(m + 1)] = int32_t(hcols.size());
+        for (int32_t c : v) send[size_t(c)] = 1;
+    }
+    // directions and diagonal in LDS; local columns in 16 bits
+    const size_t real = h.valf.p ? sizeof(float) : sizeof(double);
+    if (size_t(R + part->max_halo) * 3 * real + size_t(R) * 8 > kTeamLds || R + part->max_halo > 65536) return nullptr;
+    part->hptr.alloc(hptr.size());
+    part->hptr.upload(hptr.data(), hptr.size(), s);
+    part->hcols.alloc(std::max<size_t>(hcols.size(), 1));
+    part->hcols.upload(hcols.data(), hcols.size(), s);
+    part->send.alloc(send.size());
+    part->send.upload(send.data(), send.size(), s);
+    part->col.alloc(size_t(h.tpairs));
+    const unsigned grid = unsigned((64 * P.nslices + 255) / 256);
+    team_columns<<<grid, 256, 0, s>>>(h.scol.p, h.sptr.p, h.rowlen.p, nv, h.tptr.p, h.twid.p, int(R), part->hptr.p,
+                                      part->hcols.p, part->col.p);
+    SHELL_HIP(hipGetLastError());
+    SHELL_HIP(hipStreamSynchronize(s));  // the host lists are released on return
+    return part;
+}
+
+void build_team(shell_hessian_s& h, hipStream_t s) {
+    const SellPattern& P = h.pat;
+    const int64_t nv = P.nv;
+    if (!nv) return;
+    const int64_t R = team_rows(nv);
+    if (R > kTeamMaxRows) return;
+    // slices of pairs
+    std::vector<int64_t> tptr(size_t(P.nslices + 1), 0);
+    std::vector<int32_t> twid(size_t(P.nslices), 1);
+    for (int64_t sl = 0; sl < P.nslices; ++sl) {
+        int w = 1;
+        for (int64_t i = 64 * sl; i < std::min(nv, 64 * sl + 64); ++i)
+            w = std::max(w, (P.rowlen[size_t(i)] - (P.dslot[size_t(i)] >= 0 ? 1 : 0) + 1) / 2);
+        twid[size_t(sl)] = w;
+        tptr[size_t(sl + 1)] = tptr[size_t(sl)] + 64 * int64_t(w);
+    }
+    h.tpairs = tptr[size_t(P.nslices)];
+    h.tptr.alloc(tptr.size());
+    h.tptr.upload(tptr.data(), tptr.size(), s);
+    h.twid.alloc(twid.size());
+    h.twid.upload(twid.data(), twid.size(), s);
+    SHELL_HIP(hipStreamSynchronize(s));
+    auto part = build_part(h, R, s);
+    if (!part) {
+        h.tptr.release();
+        h.twid.release();
+        return;
+    }
+    const unsigned grid = unsigned((64 * P.nslices + 255) / 256);
+    if (h.valf.p) {
+        h.tvalf.alloc(size_t(2 * h.tpairs));
+        team_values<float><<<grid, 256, 0, s>>>(h.scol.p, h.val.p, h.sptr.p, h.rowlen.p, nv, h.tptr.p, h.twid.p,
+                                                h.tvalf.p);
+    } else {
+        h.tval.alloc(size_t(2 * h.tpairs));
+        team_values<double><<<grid, 256, 0, s>>>(h.scol.p, h.val.p, h.sptr.p, h.rowlen.p, nv, h.tptr.p, h.twid.p,
+                                                 h.tval.p);
+    }
+    SHELL_HIP(hipGetLastError());
+    SHELL_HIP(hipStreamSynchronize(s));
+    h.parts.push_back(std::move(part));
+}
+
+const TeamPart* team_part(shell_hessian_s& h, int64_t rows, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(h.parts_mutex);
+    if (h.parts.empty()) return nullptr;
+    const TeamPart* own = h.parts[0].get();
+    if (rows <= own->rows || own->members == 1) return own;
+    for (const auto& p : h.parts)
+        if (p->rows == rows) return p.get();
+    auto part = build_part(h, rows, s);
+    if (!part) return own;
+    h.parts.push_back(std::move(part));
+    return h.parts.back().get();
 }
 
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,

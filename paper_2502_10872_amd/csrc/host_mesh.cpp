@@ -32,6 +32,18 @@ void parallel_for(int64_t n, F&& fn) {
 
 }  // namespace
 
+void host_parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn, int64_t small) {
+    const int64_t nt = std::max<int64_t>(1, std::min<int64_t>({16, int64_t(std::thread::hardware_concurrency()), n}));
+    if (n < small || nt == 1) {
+        if (n > 0) fn(0, n);
+        return;
+    }
+    std::vector<std::thread> th;
+    const int64_t chunk = (n + nt - 1) / nt;
+    for (int64_t a = 0; a < n; a += chunk) th.emplace_back([=, &fn] { fn(a, std::min(n, a + chunk)); });
+    for (auto& t : th) t.join();
+}
+
 HostTopology build_topology(int model, int64_t nv, int64_t nt, const int32_t* tris, int64_t n_clamped,
                             const int32_t* clamped) {
     HostTopology topo;

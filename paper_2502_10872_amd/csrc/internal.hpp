@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <functional>
 #include <stdexcept>
 #include <string>
 #include <memory>
@@ -180,6 +181,11 @@ struct SellPattern {
 };
 constexpr int kRowGroup = 512;     // rows per work item (and threads per work-group) of the row kernels
 constexpr int kMaxGroupCols = 4096;  // largest column set staged in LDS (larger: direct gathers)
+// runs fn(first, last) over [0, n) on the host's threads; ranges in chunks, n below `small` on this thread
+void host_parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn, int64_t small = 1);
+// team solves (team.hpp): most rows of a member, and the LDS for its directions (two kilobytes short of a CU's)
+constexpr int kTeamMaxRows = 4096;
+constexpr size_t kTeamLds = 158 * 1024;
 // staging: build the row groups' column lists (used when every group fits kMaxGroupCols)
 SellPattern build_sell_pattern(const std::vector<int32_t>& idx, int k, int64_t ns, int64_t nv, bool staging);
 
@@ -206,8 +212,10 @@ struct ForceDesc {
 struct PcgState {
     double rz[3], rr[3], tol2[3], alpha[3], beta[3];
     double gsq;
+    double sample[2];               // team solve: summed wall-clock ticks of the sampled products and updates
     int32_t iters[3], target[3], active[3];
     int32_t done, budget, replay, nonfinite;
+    int32_t samples, gone;          // team solve: iterations sampled; (state 0) a member gave up waiting
 };
 
 struct SolveDesc {
@@ -243,6 +251,17 @@ struct SolveDesc {
     double tol2_abs[3];             // > 0: the stop test's bound on r.r as given (a refinement pass keeps
                                     // the first pass's); 0: rtol2 times the initial r.r
     const double* rq;               // mixed refinement: the float64 product (M + dt^2 K_s) y64
+    // team solve: off-diagonal entries in pairs (value pairs, packed pairs of 16-bit local columns), the
+    // members' halo columns, which rows other members read, the exchange rows and slots
+    const void* tval;
+    const uint32_t* tcol;
+    const int64_t* tptr;
+    const int32_t* twid;
+    const int32_t* hptr;
+    const int32_t* hcols;
+    const uint8_t* tsend;
+    double* slots;
+    int32_t trows, tmembers;
 };
 
 struct WorkItem {
@@ -301,9 +320,34 @@ struct shell_stencils_s {
     shell::DevArray<shell::WorkItem> tile_items; // (0, tile) for every tile
 };
 
+namespace shell {
+// How the rows of K_s are dealt to the members of a team (team.hpp): `rows` consecutive rows each.  A
+// member's column ids are its own rows' offsets, then `rows` + the index in its list of halo columns.
+struct TeamPart {
+    int32_t rows = 0, members = 0, max_halo = 0;
+    DevArray<int32_t> hptr, hcols;  // each member's halo columns, ascending
+    DevArray<uint32_t> col;         // [pairs] two local column ids
+    DevArray<uint8_t> send;         // [nv] 1: some other member reads this row
+    size_t bytes() const { return hptr.bytes() + hcols.bytes() + col.bytes() + send.bytes(); }
+};
+}  // namespace shell
+
 struct shell_hessian_s {
     shell_stencils_s* st = nullptr;
     shell::SellPattern pat;
+    // off-diagonal entries for team solves, in the stencils' precision: slice s holds twid[s] pairs of
+    // entries per row, pair k of row i at slot tptr[s] + 64 k + i % 64 (a value pair, and a column pair in
+    // the part); padding holds zeros and the row's own column
+    int64_t tpairs = 0;
+    shell::DevArray<int64_t> tptr;
+    shell::DevArray<int32_t> twid;
+    shell::DevArray<double> tval;
+    shell::DevArray<float> tvalf;
+    // the parts in use: the first for a simulation on its own, the others (made on first use, under the lock)
+    // for batches, whose meshes take larger members so that more of them run together; none: no team solves
+    // (direct product, or rows too scattered)
+    std::vector<std::unique_ptr<shell::TeamPart>> parts;
+    std::mutex parts_mutex;
     shell::DevArray<int32_t> scol;       // [nslots]
     shell::DevArray<int32_t> width;      // [nslices]
     shell::DevArray<int64_t> sptr;       // [nslices+1]
@@ -416,6 +460,7 @@ struct shell_sim_s {
     shell::DevArray<double> p, p2, q;    // PCG work vectors (float in mixed; sized in doubles)
     shell::DevArray<float> z;            // mixed only: the preconditioned residual, read by the product
     shell::DevArray<double> bins;        // PCG dot-product bins
+    shell::DevArray<double> slots;       // team solve: the members' sums
     shell::DevArray<double> partials;    // reduction partials
     // quasi-static solves only: zero mass, the applied load (internal order), the Newton step's scale
     shell::DevArray<double> zmass, fext, ustep;
@@ -490,6 +535,7 @@ struct shell_batch_s {
     shell::DevArray<shell::WorkItem> items;   // [rows | tiles of each model]
     shell::DevArray<int32_t> mlist;
     bool membrane = false;  // simulations with the membrane: the members' steps interleave on their own streams
+    uint64_t team_wait = ~uint64_t(0);  // ticks a team's wait may take (tests shorten it)
 };
 
 namespace shell {
@@ -535,6 +581,10 @@ void launch_scatter_rows(const void* src, const int32_t* perm, void* dst, int64_
 void launch_assemble(shell_hessian_s& h, hipStream_t s);
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,
                   hipStream_t s);
+// the layout of team solves (h.parts stays empty where a team cannot take the mesh); synchronises s
+void build_team(shell_hessian_s& h, hipStream_t s);
+// the part whose members hold at least `rows` rows (0: the simulation's own), or null; may synchronise s
+const TeamPart* team_part(shell_hessian_s& h, int64_t rows, hipStream_t s);
 // solver.hip
 void sim_alloc(shell_sim_s& sim);
 void batch_init(shell_batch_s& b);

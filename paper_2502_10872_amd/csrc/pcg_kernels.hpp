@@ -196,16 +196,20 @@ __global__ __launch_bounds__(kBlk) void k_residual(const SolveDesc* __restrict__
     if (threadIdx.x == 0) d.part[wi.unit] = acc[0];
 }
 
-// |g|^2 of each mesh; also zeroes the dot-product partials of the coming solve
+// |g|^2 of each mesh
 __global__ __launch_bounds__(kRedBlk) void k_fin_residual(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ meshes) {
     const SolveDesc& d = descs[meshes[blockIdx.x]];
     double tot[1];
     reduce_partials<1>(d.part, d.ngroups, tot);
-    bin_clear_all(d);
     if (threadIdx.x == 0) {
         d.st[0].gsq = tot[0];
         d.st[0].nonfinite = !isfinite(tot[0]);
     }
+}
+
+// zeroes the dot-product partials of the coming solve
+__global__ __launch_bounds__(kRedBlk) void k_bin_clear(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ meshes) {
+    bin_clear_all(descs[meshes[blockIdx.x]]);
 }
 
 // What the rest of a product needs of the recurrence state.

@@ -6,16 +6,20 @@
 // Every kernel takes an array of per-mesh descriptors and a list of (mesh, 512-row group) work items,
 // so one launch per phase advances any set of meshes (a single simulation is a set of one).
 //
-// Every scalar of the recurrences lives on the device.  A PCG iteration is two streaming kernels: the
-// product kernel advances the recurrence state by the previous update (beta, activity flags, counts),
-// forms the new search direction p = z + beta p_old for its row group's distinct columns while staging
-// them in LDS, writes p for its own rows and q = A p; the update kernel computes alpha and advances y
-// and r.  The dot products reach the next kernel as per-work-group partials in fixed slots, summed in
-// a fixed order by every work-group that needs them (see the partials in pcg_kernels.hpp), so no
-// reduction kernel sits between them and the result does not depend on scheduling.  p alternates
-// between two buffers because other row groups still read the previous direction while it is
-// rewritten.  Kernels of converged meshes return at once, so the host launches iterations in chunks and
-// reads the flags once per chunk.
+// Every scalar of the recurrences lives on the device.  A solve runs as teams of resident work-groups, one
+// kernel per solve (team_pcg.hpp), wherever the meshes have a team layout; otherwise as a chain of two
+// streaming kernels per iteration: the product kernel advances the recurrence state by the previous update
+// (beta, activity flags, counts), forms the new search direction p = z + beta p_old for its row group's
+// distinct columns while staging them in LDS, writes p for its own rows and q = A p; the update kernel
+// computes alpha and advances y and r.  The chain's dot products reach the next kernel as per-work-group
+// partials in fixed slots, summed in a fixed order by every work-group that needs them (see the partials in
+// pcg_kernels.hpp), so no reduction kernel sits between them; in both forms the result does not depend on
+// scheduling.  p alternates between two buffers because other row groups still read the previous direction
+// while it is rewritten.  The chain's kernels return at once for converged meshes, so the host launches
+// iterations in chunks and reads the flags once per chunk.
+//
+// Per iteration, team against chain, SS sphere caps, FP64 and mixed: 4.4 / 3.8 us against 20 at 484 vertices, 7.6 /
+// 7.4 against 21 at 4225, 11.5 / 10.9 against 26 / 24 at 65536, 42 / 31 against 107 / 71 at 1048576.
 //
 // Precision: FP64 throughout, or mixed: float32 matrix values (applied in difference form), Jacobi
 // diagonal and the vectors p, q, z and f; the increment y in float32 folded into float64 every 16
@@ -30,6 +34,7 @@
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "pcg_kernels.hpp"
+#include "team_pcg.hpp"
 
 namespace shell {
 
@@ -70,6 +75,46 @@ GraphCache::~GraphCache() {
     if (capture) (void)hipStreamDestroy(capture);
 }
 
+void TeamSlots::ensure() {
+    if (capacity_) return;
+    int dev = 0;
+    SHELL_HIP(hipGetDevice(&dev));
+    SHELL_HIP(hipDeviceGetAttribute(&capacity_, hipDeviceAttributeMultiprocessorCount, dev));
+    free_ = capacity_;
+}
+
+TeamSlots& TeamSlots::of_current_device() {
+    constexpr int kMaxDevices = 64;
+    static TeamSlots slots[kMaxDevices];
+    int dev = 0;
+    SHELL_HIP(hipGetDevice(&dev));
+    SHELL_CHECK(dev >= 0 && dev < kMaxDevices, SHELL_E_UNSUPPORTED, "device ordinal beyond the admission table");
+    std::lock_guard<std::mutex> lk(slots[dev].m_);
+    slots[dev].ensure();
+    return slots[dev];
+}
+
+void TeamSlots::acquire(int n) {
+    std::unique_lock<std::mutex> lk(m_);
+    cv_.wait(lk, [&] { return free_ >= n; });
+    free_ -= n;
+}
+
+bool TeamSlots::try_acquire(int n) {
+    std::lock_guard<std::mutex> lk(m_);
+    if (free_ < n) return false;
+    free_ -= n;
+    return true;
+}
+
+void TeamSlots::release(int n) {
+    {
+        std::lock_guard<std::mutex> lk(m_);
+        free_ += n;
+    }
+    cv_.notify_all();
+}
+
 StepProfiler::~StepProfiler() {
     for (const Sample& e : pending) {
         pool.push_back(e.a);
@@ -88,6 +133,7 @@ struct Launch {
     long nrows;
     const WorkItem* tiles[6];
     long ntiles[6];
+    const WorkItem* team;  // (mesh, member) of the launch set's teams
     const int32_t* meshes;
     int nmeshes;
     int precision;
@@ -228,11 +274,12 @@ void forces(const Launch& L, hipStream_t s, StepProfiler* prof = nullptr) {
 }
 
 struct ItemBuilder {
-    std::vector<WorkItem> rows, tiles[6];
+    std::vector<WorkItem> rows, tiles[6], team;
     std::vector<int32_t> meshes;
     void build(const std::vector<shell_sim_s*>& sims, const std::vector<int>& subset) {
         rows.clear();
         meshes.clear();
+        team.clear();
         for (auto& t : tiles) t.clear();
         for (int m : subset) {
             const shell_sim_s& sim = *sims[size_t(m)];
@@ -248,7 +295,7 @@ struct ItemBuilder {
 // have finished before either is overwritten.
 Launch upload(shell_batch_s& b, const ItemBuilder& ib, hipStream_t s, int pcg_workgroups = SHELL_PCG_WORKGROUPS) {
     SHELL_HIP(hipStreamSynchronize(s));
-    size_t total = ib.rows.size();
+    size_t total = ib.rows.size() + ib.team.size();
     for (const auto& t : ib.tiles) total += t.size();
     if (total > b.items_cap || !b.items_host) {
         {
@@ -271,6 +318,9 @@ Launch upload(shell_batch_s& b, const ItemBuilder& ib, hipStream_t s, int pcg_wo
         L.ntiles[m] = long(ib.tiles[m].size());
         off += ib.tiles[m].size();
     }
+    std::copy(ib.team.begin(), ib.team.end(), b.items_host + off);
+    L.team = b.items.p + off;
+    off += ib.team.size();
     std::copy(ib.meshes.begin(), ib.meshes.end(), b.mlist_host);
     if (off) SHELL_HIP(hipMemcpyAsync(b.items.p, b.items_host, off * sizeof(WorkItem), hipMemcpyHostToDevice, s));
     if (!ib.meshes.empty())
@@ -322,7 +372,7 @@ void read_states(shell_batch_s& b, hipStream_t s) {
     if (b.prof) b.prof->drain();
 }
 
-SolveDesc solve_desc(shell_sim_s& sim, PcgState* st) {
+SolveDesc solve_desc(shell_sim_s& sim, PcgState* st, const TeamPart* tp = nullptr) {
     SolveDesc d{};
     d.x = sim.x.p;
     d.X = sim.st->X.p;
@@ -357,6 +407,19 @@ SolveDesc solve_desc(shell_sim_s& sim, PcgState* st) {
     d.bins = sim.bins.p;
     d.nv = sim.nv;
     d.ngroups = blocks(sim.nv);
+    if (tp) {
+        d.tval = sim.st->precision == SHELL_PREC_MIXED ? static_cast<const void*>(sim.h->tvalf.p)
+                                                       : static_cast<const void*>(sim.h->tval.p);
+        d.tcol = tp->col.p;
+        d.tptr = sim.h->tptr.p;
+        d.twid = sim.h->twid.p;
+        d.hptr = tp->hptr.p;
+        d.hcols = tp->hcols.p;
+        d.tsend = tp->send.p;
+        d.slots = sim.slots.p;
+        d.trows = tp->rows;
+        d.tmembers = tp->members;
+    }
     return d;
 }
 
@@ -382,6 +445,52 @@ ForceDesc force_desc(shell_sim_s& sim) {
     return d;
 }
 
+// ------------------------------------------------------------------ team solves
+
+// Iterations of one launch at most (a launch of the largest meshes then takes some 0.3 s).
+constexpr int kTeamChunk = 8192;
+
+template <typename VR, typename MR>
+void launch_team(const Launch& L, const WorkItem* items, int members, int rows, size_t lds, int mode, int limit,
+                 int every, uint64_t wait, hipStream_t s) {
+    auto go = [&](auto kernel) {
+        kernel<<<unsigned(members), kTeamThreads, lds, s>>>(L.sdesc, items, mode, limit, every, wait);
+    };
+    const int rpl = (rows + kTeamThreads - 1) / kTeamThreads;
+    if (rpl <= 1) go(k_team_pcg<VR, MR, 1>);
+    else if (rpl <= 2) go(k_team_pcg<VR, MR, 2>);
+    else if (rpl <= 3) go(k_team_pcg<VR, MR, 3>);
+    else if (rpl <= 4) go(k_team_pcg<VR, MR, 4>);
+    else if (rpl <= 6) go(k_team_pcg<VR, MR, 6>);
+    else go(k_team_pcg<VR, MR, 8>);
+    SHELL_HIP(hipGetLastError());
+}
+
+// The parts of the meshes' teams, or none: a mesh has no team layout, or a launch shape of the kernel chain was
+// asked for.  A float64 batch keeps the chain too: its members are small, stiff meshes whose solves stop on a
+// budget, and there regrouping the dot products alone moved the result by 1e-8 to 1e-7 (4 of 17 random
+// batches; no step of 60 single meshes moved by more than 2e-11, no mixed-precision batch by more than its own
+// precision), past the nine digits that stepping the batch has always repeated.  A mixed-precision batch whose members would not all be resident together takes larger members (up to 2048 rows:
+// a unit then advances 146 rows a microsecond, against 60 with 512, 97 with 1024 and 132 with 4096), and what
+// still does not fit runs one group of meshes after another.
+std::vector<const TeamPart*> team_parts(const shell_batch_s& b, int pcg_workgroups, hipStream_t s) {
+    std::vector<const TeamPart*> parts;
+    if (pcg_workgroups > 0 || (b.sims.size() > 1 && b.precision == SHELL_PREC_FP64)) return parts;
+    const int cus = TeamSlots::of_current_device().capacity();
+    for (int64_t rows : {0, 512, 1024, 1536, 2048}) {
+        int64_t members = 0;
+        for (const shell_sim_s* sim : b.sims) {
+            const TeamPart* own = team_part(*sim->h, 0, s);
+            if (!own) return parts;
+            members += rows > own->rows ? (sim->nv + rows - 1) / rows : own->members;
+        }
+        if (b.sims.size() > 1 && members > cus && rows < 2048) continue;
+        for (const shell_sim_s* sim : b.sims) parts.push_back(team_part(*sim->h, rows, s));
+        break;
+    }
+    return parts;
+}
+
 struct MeshStep {
     const shell_step_params_t* prm = nullptr;
     shell_step_stats_t stats{};
@@ -404,6 +513,8 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
     const int n = int(b.sims.size());
     const int wg = prms[0].pcg_workgroups > 0 ? prms[0].pcg_workgroups : SHELL_PCG_WORKGROUPS;
     const bool graphs = (prms[0].flags & SHELL_STEP_NO_GRAPHS) == 0;
+    const std::vector<const TeamPart*> parts = team_parts(b, prms[0].pcg_workgroups, s);
+    const bool teams = !parts.empty();
     std::vector<MeshStep> ms(static_cast<size_t>(n));
     SHELL_HIP(hipStreamSynchronize(s));  // the descriptor staging is reused below
     if (b.fdesc_dirty) {
@@ -415,7 +526,7 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         MeshStep& st = ms[size_t(m)];
         st.prm = &prms[nparams == 1 ? 0 : m];
         shell_sim_s& sim = *b.sims[size_t(m)];
-        SolveDesc d = solve_desc(sim, b.state.p + 2 * m);
+        SolveDesc d = solve_desc(sim, b.state.p + 2 * m, teams ? parts[size_t(m)] : nullptr);
         d.dt = st.prm->dt;
         d.dt2 = d.dt * d.dt;
         for (int c = 0; c < 3; ++c) d.grav[c] = st.prm->gravity[c];
@@ -485,13 +596,8 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
             solve.push_back(m);
         }
         if (solve.empty()) break;
-        // One PCG solve over the meshes of `set`: per-mesh targets and the slot ranges of its launch shape
-        // (upload() drains the stream first, so the staging is idle), the first kernel (from r = -g, or
-        // for a refinement pass from the true residual of the increment so far), the first product, then
-        // chunks until every mesh is done.  Returns the last product launched.
-        auto run_pcg = [&](const std::vector<int>& set, bool refine) -> long {
-            ib.build(b.sims, set);
-            L = upload(b, ib, s, wg);
+        // The targets of one solve over the meshes of `set`, into the staged descriptors.
+        auto set_targets = [&](const std::vector<int>& set, bool refine) {
             for (int m : set) {
                 const shell_step_params_t& p = *ms[size_t(m)].prm;
                 SolveDesc& d = b.sdesc_host[m];
@@ -501,19 +607,96 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
                     d.tol2_abs[c] = refine ? ms[size_t(m)].tol2[c] : 0.0;
                 }
             }
+        };
+        // A refinement pass starts from the true residual of the increment so far.
+        auto refine_start = [&](const std::vector<int>& set) {
+            k_pcg_fold<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
+            for (int m : set) {
+                shell_sim_s& sim = *b.sims[size_t(m)];
+                const SolveDesc& d = b.sdesc_host[m];
+                launch_apply(*sim.h, d.mass, d.dt2, sim.y64.p, sim.rq.p, s);
+            }
+            k_pcg_refine_init<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, L.per_u);
+        };
+        // The solve by teams: the meshes in groups whose members fit the compute units together, each group
+        // one launch (more when a solve is longer than a launch may be).  False when a member gave up
+        // waiting: the solve is then to be run again as a chain.
+        auto team_pcg = [&](const std::vector<int>& set, bool refine) -> bool {
+            TeamSlots& cu = TeamSlots::of_current_device();
+            struct Group {
+                size_t first = 0;
+                int members = 0, rows = 0;
+                size_t lds = 0;
+            };
+            std::vector<int> left = set;
+            int limit = kTeamChunk, mode = refine ? kTeamRefine : kTeamFresh;
+            for (int m : set)
+                if (ms[size_t(m)].prm->chunk > 0) limit = std::min(limit, int(ms[size_t(m)].prm->chunk));
+            const int every = b.prof ? b.prof->every : 0;
+            set_targets(set, refine);
+            while (!left.empty()) {
+                std::vector<int> order = left;
+                std::stable_sort(order.begin(), order.end(), [&](int p, int q) {
+                    return parts[size_t(p)]->rows > parts[size_t(q)]->rows;
+                });
+                ib.build(b.sims, left);
+                std::vector<Group> groups;
+                for (int m : order) {
+                    const TeamPart& tp = *parts[size_t(m)];
+                    if (groups.empty() || groups.back().members + tp.members > cu.capacity())
+                        groups.push_back({ib.team.size(), 0, 0, 0});
+                    Group& g = groups.back();
+                    for (int q = 0; q < tp.members; ++q) ib.team.push_back({m, q});
+                    g.members += tp.members;
+                    g.rows = std::max(g.rows, int(tp.rows));
+                    g.lds = std::max(g.lds, team_lds<VR>(tp.rows, tp.max_halo));
+                }
+                L = upload(b, ib, s, wg);
+                upload_descs(b, s);
+                if (mode == kTeamRefine) refine_start(left);
+                k_team_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
+                int most = 0;
+                for (const Group& g : groups) most = std::max(most, g.members);
+                {
+                    TeamLease lease(cu, most);
+                    for (const Group& g : groups)
+                        launch_team<VR, MR>(L, L.team + g.first, g.members, g.rows, g.lds, mode, limit, every,
+                                            std::min(b.team_wait, kTeamWaitTicks), s);
+                    read_states(b, s);
+                }
+                std::vector<int> next;
+                for (int m : left) {
+                    const PcgState& ps = b.state_host[2 * m + 1];
+                    if (b.state_host[2 * m].gone) return false;
+                    if (every > 0)
+                        for (int ph = 0; ph < 2; ++ph) {
+                            const int phase = ph ? SHELL_PHASE_UPDATE : SHELL_PHASE_PRODUCT;
+                            b.prof->ms[phase] += ps.sample[ph] * 1e-5;  // 100 MHz ticks
+                            b.prof->count[phase] += ps.samples;
+                        }
+                    if (!ps.done) next.push_back(m);
+                }
+                left = next;
+                mode = kTeamResume;
+            }
+            return true;
+        };
+        // One PCG solve over the meshes of `set`: by teams, or as a chain of kernels: per-mesh targets and
+        // the slot ranges of its launch shape (upload() drains the stream first, so the staging is idle), the
+        // first kernel (from r = -g, or for a refinement pass from the true residual of the increment so
+        // far), the first product, then chunks until every mesh is done.  Returns the last product launched.
+        auto run_pcg = [&](const std::vector<int>& set, bool refine) -> long {
+            if (teams && team_pcg(set, refine)) return 0;
+            ib.build(b.sims, set);
+            L = upload(b, ib, s, wg);
+            set_targets(set, refine);
             set_slot_ranges(b, L, ib);
             upload_descs(b, s);
-            if (refine) {
-                k_pcg_fold<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
-                for (int m : set) {
-                    shell_sim_s& sim = *b.sims[size_t(m)];
-                    const SolveDesc& d = b.sdesc_host[m];
-                    launch_apply(*sim.h, d.mass, d.dt2, sim.y64.p, sim.rq.p, s);
-                }
-                k_pcg_refine_init<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, L.per_u);
-            } else {
+            k_bin_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
+            if (refine)
+                refine_start(set);
+            else
                 k_pcg_init<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, L.per_u);
-            }
             timed_launch(b.prof.get(), b.prof && b.prof->every > 0, SHELL_PHASE_PRODUCT, s,
                          [&](hipEvent_t e0, hipEvent_t e1) {
                              hipExtLaunchKernelGGL(k_pcg_spmv<VR, MR>, dim3(unsigned(L.pcg_grid)), dim3(kBlk),
@@ -670,6 +853,7 @@ void time_impl(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out,
         forces(L, s);
         k_residual<VR><<<grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, 0);
         k_fin_residual<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
+        k_bin_clear<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
         k_pcg_init<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, L.per_u);
         k_pcg_spmv<VR, MR><<<L.pcg_grid, kBlk, L.lds_spmv, s>>>(L.sdesc, L.rows, L.nrows, 0, L.per);
         k_pcg_update<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, 0, L.per_u);
@@ -688,6 +872,38 @@ void time_impl(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out,
     out.reps = reps;
     // the force kernels alone
     out.force_ms = timed([&] { forces(L, s); });
+    if (const TeamPart* tp = team_part(*sim.h, 0, s)) {
+        // the step's solve is one kernel: its phases over `reps` iterations, from the kernel's own clock
+        SolveDesc dt_ = solve_desc(sim, b.state.p, tp);
+        dt_.dt = d.dt;
+        dt_.dt2 = d.dt2;
+        dt_.replay = 1;
+        for (int c = 0; c < 3; ++c) dt_.target[c] = reps + 1;
+        init();
+        SHELL_HIP(hipStreamSynchronize(s));
+        b.sdesc_host[0] = dt_;
+        upload_descs(b, s);
+        for (int q = 0; q < tp->members; ++q) ib.team.push_back({0, q});
+        L = upload(b, ib, s);
+        k_team_clear<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
+        {
+            TeamLease lease(TeamSlots::of_current_device(), tp->members);
+            launch_team<VR, MR>(L, L.team, tp->members, tp->rows, team_lds<VR>(tp->rows, tp->max_halo), kTeamFresh,
+                                1 << 30, 1, kTeamWaitTicks, s);
+            read_states(b, s);
+        }
+        const PcgState& ps = b.state_host[1];
+        if (!b.state_host[0].gone && ps.samples > 0) {
+            out.spmv_ms = ps.sample[0] * 1e-5 / ps.samples;
+            out.update_ms = ps.sample[1] * 1e-5 / ps.samples;
+            (void)hipEventDestroy(e0);
+            (void)hipEventDestroy(e1);
+            return;
+        }
+        b.sdesc_host[0] = d;
+        set_slot_ranges(b, L, ib);
+        upload_descs(b, s);
+    }
     // repeated launches of one iteration's kernel: each re-reads the same state and partials
     init();
     out.spmv_ms = timed([&] {
@@ -710,6 +926,7 @@ void sim_alloc(shell_sim_s& sim) {
     for (auto* a : {&sim.x, &sim.v, &sim.xt, &sim.xhat, &sim.g, &sim.y, &sim.r, &sim.f, &sim.p, &sim.p2, &sim.q})
         a->alloc(size_t(std::max(n3, 1L)));
     sim.bins.alloc(size_t(2 * 2 * kBinQ * kSlots));
+    if (const TeamPart* own = team_part(*sim.h, 0, nullptr)) sim.slots.alloc(team_slot_count(own->members));
     if (sim.st->precision == SHELL_PREC_MIXED) {
         sim.z.alloc(size_t(std::max(n3, 1L)));
         sim.y64.alloc(size_t(std::max(n3, 1L)));
@@ -805,6 +1022,11 @@ shell_status_t batch_step(shell_batch_s& b, const shell_step_params_t* p, int np
     }
     if (b.precision == SHELL_PREC_MIXED) return step_impl<float, float>(b, p, nparams, stats, s, qs);
     return step_impl<double, double>(b, p, nparams, stats, s, qs);
+}
+
+// test hook: the ticks (10 ns) a team's wait of this simulation's own steps may take
+extern "C" void shell_test_team_wait(shell_sim_s* sim, uint64_t ticks) {
+    if (sim && sim->solo) sim->solo->team_wait = ticks;
 }
 
 void batch_time_kernels(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out, hipStream_t s) {

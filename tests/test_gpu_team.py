@@ -1,0 +1,111 @@
+"""Solves by resident teams of work-groups against the same solves as a chain of kernels.
+
+`pcg_workgroups` asks for a launch shape of the kernel chain, so the same step with and without it compares
+the two: the same recurrence with its dot products grouped otherwise.  Sizes sit at the edges of the team
+layout: one member up to 1024 rows, members of 256 rows up to 16384, of 512 above, then one member per compute
+unit with several rows per thread; ragged last slices throughout.  Twenty replayed iterations keep the
+rounding's growth small: FP64 agrees to 1e-10 (the oracle parity bound), mixed precision to 1e-5 (the bound of
+the full-size mixed iteration against the oracle)."""
+
+import ctypes
+
+import numpy as np
+import pytest
+import torch  # noqa: F401  (its HIP runtime is the one the library shares)
+
+from paper_2502_10872_amd import inputs as I
+from paper_2502_10872_amd import shell as S
+
+pytestmark = pytest.mark.gpu
+MAT = I.MATERIAL
+BOUND = {S.SHELL_PREC_FP64: 1e-10, S.SHELL_PREC_MIXED: 1e-5}
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def _start(mesh):
+    g = I.rng(11)
+    n = mesh.meta["n"]
+    s, t = np.tile(np.linspace(0, 1, n), n), np.repeat(np.linspace(0, 1, n), n)
+    u = 0.002 * mesh.spacing * n * np.sin(2 * np.pi * s) * np.sin(2 * np.pi * t)
+    return mesh.X + u[:, None] * g.uniform(0.5, 1.0, 3), 0.1 * np.sin(np.pi * s * t)[:, None] * g.uniform(0.5, 1.0, 3)
+
+
+def _step(pb, mesh, x, v, wg=0, newton=2, iters=20, **kw):
+    S.shell_sim_set_state(pb.sim, x, v, 0)
+    counts = np.full((newton, 3), iters, np.int32)
+    params, _keep = S.step_params(1 / 60, max_newton=newton, newton_rtol=0.0, replay=counts, pcg_workgroups=wg, **kw)
+    rc, st = S.shell_step_implicit(pb.sim, params)
+    xo, vo, _ = S.shell_sim_get_state(pb.sim, mesh.nv)
+    return xo, vo, st
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("model,n", [("SS", 5), ("EP", 22), ("SS", 23), ("FS", 32), ("ES", 33), ("SS", 127), ("EP", 129),
+                                     ("FS", 363), ("SS", 420), ("SS", 600), ("SS", 850)])
+def test_team_solves_equal_the_kernel_chain(model, n, precision):
+    mesh = I.plate_mesh(n, 1.0, 0.2, 7, model) if model.endswith("P") else I.workload_sphere_cap(n, model)
+    x, v = _start(mesh)
+    with S.Problem(mesh, MAT, precision=precision) as pb:
+        xa, va, sa = _step(pb, mesh, x, v)
+        xb, vb, sb = _step(pb, mesh, x, v, wg=512)
+    assert np.array_equal(sa["counts"], sb["counts"])
+    assert rel(xa - mesh.X, xb - mesh.X) <= BOUND[precision]
+    assert rel(va, vb) <= BOUND[precision]
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+def test_a_solve_over_several_launches_is_the_same_solve(precision):
+    """`chunk` bounds the iterations of one launch: the solve pauses and resumes on the same bits."""
+    mesh = I.workload_cylinder(70, "SS")
+    x, v = _start(mesh)
+    with S.Problem(mesh, MAT, precision=precision) as pb:
+        xa, va, _ = _step(pb, mesh, x, v)
+        xb, vb, _ = _step(pb, mesh, x, v, chunk=7)
+    assert np.array_equal(xa, xb) and np.array_equal(va, vb)
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+def test_held_coordinates_and_batches_of_teams(precision):
+    """A batch (mixed precision: teams of one launch), one mesh with single coordinates held, against each mesh
+    alone through the kernel chain."""
+    meshes = [I.workload_cylinder(40, "SS"), I.plate_mesh(21, 1.0, 0.2, 7, "EP"), I.workload_sphere_cap(60, "FS")]
+    held = [np.arange(m.nv) % 5 * (np.arange(m.nv) % 7 == 0) if k == 0 else None for k, m in enumerate(meshes)]
+    probs = [S.Problem(m, MAT, precision=precision, held=h) for m, h in zip(meshes, held)]
+    try:
+        starts = [_start(m) for m in meshes]
+        chain = [_step(pb, m, x, v, wg=512)[:2] for pb, m, (x, v) in zip(probs, meshes, starts)]
+        for pb, (x, v) in zip(probs, starts):
+            S.shell_sim_set_state(pb.sim, x, v, 0)
+        batch = S.shell_batch_create([pb.sim for pb in probs])
+        try:
+            params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=0.0, replay=np.full((2, 3), 20, np.int32))
+            S.shell_batch_step(batch, params, len(probs))
+        finally:
+            S.shell_destroy_batch(batch)
+        for pb, m, (xc, vc) in zip(probs, meshes, chain):
+            x, v, _ = S.shell_sim_get_state(pb.sim, m.nv)
+            assert rel(x - m.X, xc - m.X) <= BOUND[precision] and rel(v, vc) <= BOUND[precision], m.name
+    finally:
+        for pb in probs:
+            pb.close()
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+def test_a_member_that_gives_up_hands_the_solve_to_the_chain(precision):
+    """With no time to wait the first unmet meeting ends the launch (every member leaves by itself), and the step
+    takes the kernel chain: the same bits as the step that asked for it."""
+    mesh = I.workload_cylinder(100, "SS")
+    x, v = _start(mesh)
+    limit = S.lib().shell_test_team_wait
+    limit.argtypes, limit.restype = [ctypes.c_void_p, ctypes.c_uint64], None
+    with S.Problem(mesh, MAT, precision=precision) as pb:
+        xb, vb, _ = _step(pb, mesh, x, v, wg=512)
+        limit(pb.sim, 0)
+        xa, va, _ = _step(pb, mesh, x, v)
+        limit(pb.sim, 2 ** 64 - 1)
+        xc, vc, _ = _step(pb, mesh, x, v)
+    assert np.array_equal(xa, xb) and np.array_equal(va, vb)
+    assert rel(xc - mesh.X, xb - mesh.X) <= BOUND[precision] and rel(vc, vb) <= BOUND[precision]
