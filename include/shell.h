@@ -110,11 +110,12 @@ typedef struct {
  * In mixed precision the bending and membrane forces are the float32 kernels' (widened to float64 for the
  * Newton loop), and the product reads float32 copies of K_s and of the tangent's blocks in difference
  * form, q_i = m_i p_i + dt^2 sum_j (K_s,ij I + K_m,ij)(p_j - p_i), which keeps translations in their null
- * space whatever the rounding; the vectors, dot products and the Newton loop stay float64.  On meshes of
- * 32768 vertices or more, unless SHELL_FLAG_DIRECT_PRODUCT is set, the product takes the rows in groups
- * of 128, 256 or 512 (at least 256 groups where possible) with the group's directions staged in LDS, K_s
- * from the bending Hessian's SELL-64 slots and the blocks in SELL-64 slices; smaller meshes read both as
- * CSR.
+ * space whatever the rounding; the vectors, dot products and the Newton loop stay float64.  The solve
+ * is one launch of resident work-groups where the mesh allows it (up to about 1M vertices, unless
+ * SHELL_FLAG_DIRECT_PRODUCT is set), else a chain of kernels: with the flag, or with rows too scattered to
+ * stage, the product reads both matrices as CSR; without it the rows go in groups of 128, 256 or 512 (at
+ * least 256 groups where possible) with the group's directions staged in LDS, K_s from the bending Hessian's
+ * SELL-64 slots and the blocks in SELL-64 slices.
  * A batch of such simulations steps each member as it would step alone (see shell_batch_create).  A
  * degenerate triangle is SHELL_E_DEGENERATE. */
 #define SHELL_FLAG_MEMBRANE 4

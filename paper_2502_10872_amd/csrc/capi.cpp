@@ -457,8 +457,7 @@ shell_status_t shell_assemble_constant_hessian(shell_stencils_t st, shell_stream
         if (st->precision == SHELL_PREC_MIXED) h->valf.alloc(size_t(P.nslots));
         h->kdiag.alloc(size_t(st->nv));
         launch_assemble(*h, s);
-        // with the membrane the step has a solver of its own, and the direct product was asked for
-        if ((st->cfg_flags & (SHELL_FLAG_DIRECT_PRODUCT | SHELL_FLAG_MEMBRANE)) == 0) build_team(*h, s);
+        if ((st->cfg_flags & SHELL_FLAG_DIRECT_PRODUCT) == 0) build_team(*h, s);
         *out = h.release();
         return SHELL_OK;
     });

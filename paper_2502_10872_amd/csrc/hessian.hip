@@ -219,22 +219,25 @@ void launch_assemble(shell_hessian_s& h, hipStream_t s) {
 // latencies that grows with a member's rows: 256 while one wave can read all members' sums (4225 rows: 7.6 us
 // against 8.5 with 512 and 10.5 with 1024), 512 up to as many members as compute units (32761 rows: 9.5 us
 // against 10.4 with 256), beyond that whatever keeps one member per unit.
-static int64_t team_rows(int64_t nv) {
+int64_t team_rows(int64_t nv) {
+    if (nv > 1024 && nv <= 64 * 256) return 256;
+    return team_rows_spread(nv, 1024, 512);
+}
+
+int64_t team_rows_spread(int64_t nv, int64_t alone, int64_t least) {
     int dev = 0, cus = 0;
     SHELL_HIP(hipGetDevice(&dev));
     SHELL_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     auto whole = [](int64_t n) { return (n + 63) / 64 * 64; };
-    if (nv <= 1024) return whole(nv);
-    if (nv <= 64 * 256) return 256;
-    return std::max<int64_t>(512, whole((nv + cus - 1) / cus));
+    return nv <= alone ? whole(nv) : std::max(least, whole((nv + cus - 1) / cus));
 }
 
-// The part with members of R rows, or null where it does not fit: each member's halo (the columns of its rows
-// that are other members' rows, ascending), the rows that others read, and the pairs' local columns.
-static std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, hipStream_t s) {
+std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, size_t real, hipStream_t s,
+                                     const std::vector<int64_t>* row2, const std::vector<int32_t>* col2,
+                                     std::vector<std::vector<int32_t>>* lists) {
     const SellPattern& P = h.pat;
     const int64_t nv = P.nv, members = (nv + R - 1) / R;
-    if (R > kTeamMaxRows) return nullptr;
+    if (R > kTeamMaxRows || !h.tpairs) return nullptr;
     std::vector<std::vector<int32_t>> halo(static_cast<size_t>(members));
     host_parallel_for(members, [&](int64_t a, int64_t b) {
         for (int64_t m = a; m < b; ++m) {
@@ -242,6 +245,9 @@ static std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, hipSt
             const int64_t lo = m * R, hi = std::min(nv, lo + R);
             for (int64_t e = P.rowptr[size_t(lo)]; e < P.rowptr[size_t(hi)]; ++e)
                 if (P.col[size_t(e)] < lo || P.col[size_t(e)] >= hi) v.push_back(P.col[size_t(e)]);
+            if (row2)
+                for (int64_t e = (*row2)[size_t(lo)]; e < (*row2)[size_t(hi)]; ++e)
+                    if ((*col2)[size_t(e)] < lo || (*col2)[size_t(e)] >= hi) v.push_back((*col2)[size_t(e)]);
             std::sort(v.begin(), v.end());
             v.erase(std::unique(v.begin(), v.end()), v.end());
         }
@@ -259,7 +265,6 @@ static std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, hipSt
         for (int32_t c : v) send[size_t(c)] = 1;
     }
     // directions and diagonal in LDS; local columns in 16 bits
-    const size_t real = h.valf.p ? sizeof(float) : sizeof(double);
     if (size_t(R + part->max_halo) * 3 * real + size_t(R) * 8 > kTeamLds || R + part->max_halo > 65536) return nullptr;
     part->hptr.alloc(hptr.size());
     part->hptr.upload(hptr.data(), hptr.size(), s);
@@ -273,15 +278,14 @@ static std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, hipSt
                                       part->hcols.p, part->col.p);
     SHELL_HIP(hipGetLastError());
     SHELL_HIP(hipStreamSynchronize(s));  // the host lists are released on return
+    if (lists) *lists = std::move(halo);
     return part;
 }
 
-void build_team(shell_hessian_s& h, hipStream_t s) {
+// The off-diagonal entries in pairs, in the stencils' precision.
+static void build_team_values(shell_hessian_s& h, hipStream_t s) {
     const SellPattern& P = h.pat;
     const int64_t nv = P.nv;
-    if (!nv) return;
-    const int64_t R = team_rows(nv);
-    if (R > kTeamMaxRows) return;
     // slices of pairs
     std::vector<int64_t> tptr(size_t(P.nslices + 1), 0);
     std::vector<int32_t> twid(size_t(P.nslices), 1);
@@ -297,13 +301,6 @@ void build_team(shell_hessian_s& h, hipStream_t s) {
     h.tptr.upload(tptr.data(), tptr.size(), s);
     h.twid.alloc(twid.size());
     h.twid.upload(twid.data(), twid.size(), s);
-    SHELL_HIP(hipStreamSynchronize(s));
-    auto part = build_part(h, R, s);
-    if (!part) {
-        h.tptr.release();
-        h.twid.release();
-        return;
-    }
     const unsigned grid = unsigned((64 * P.nslices + 255) / 256);
     if (h.valf.p) {
         h.tvalf.alloc(size_t(2 * h.tpairs));
@@ -315,8 +312,23 @@ void build_team(shell_hessian_s& h, hipStream_t s) {
                                                  h.tval.p);
     }
     SHELL_HIP(hipGetLastError());
-    SHELL_HIP(hipStreamSynchronize(s));
-    h.parts.push_back(std::move(part));
+    SHELL_HIP(hipStreamSynchronize(s));  // the host lists are released on return
+}
+
+void build_team(shell_hessian_s& h, hipStream_t s) {
+    if (!h.pat.nv || team_rows(h.pat.nv) > kTeamMaxRows) return;
+    build_team_values(h, s);
+    if (h.st->cfg_flags & SHELL_FLAG_MEMBRANE) return;  // its solver's part covers the tangent's columns too
+    auto part = build_part(h, team_rows(h.pat.nv), h.valf.p ? sizeof(float) : sizeof(double), s);
+    if (part) {
+        h.parts.push_back(std::move(part));
+        return;
+    }
+    h.tpairs = 0;
+    h.tptr.release();
+    h.twid.release();
+    h.tval.release();
+    h.tvalf.release();
 }
 
 const TeamPart* team_part(shell_hessian_s& h, int64_t rows, hipStream_t s) {
@@ -326,7 +338,7 @@ const TeamPart* team_part(shell_hessian_s& h, int64_t rows, hipStream_t s) {
     if (rows <= own->rows || own->members == 1) return own;
     for (const auto& p : h.parts)
         if (p->rows == rows) return p.get();
-    auto part = build_part(h, rows, s);
+    auto part = build_part(h, rows, h.valf.p ? sizeof(float) : sizeof(double), s);
     if (!part) return own;
     h.parts.push_back(std::move(part));
     return h.parts.back().get();

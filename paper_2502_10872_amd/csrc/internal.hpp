@@ -388,6 +388,10 @@ struct MembraneSolve {
     DevArray<int64_t> mptr;
     DevArray<uint16_t> slcol, mlcol;
     DevArray<int64_t> s2e;  // [slots] the CSR block of each block slot, -1 on padding
+    // team solve (team.hpp): the deal of the rows, the block slots' local columns, the members' sums
+    std::unique_ptr<TeamPart> tpart;
+    DevArray<uint16_t> tcol;
+    DevArray<double> slots;
     const int64_t* hsptr = nullptr;  // the bending Hessian's SELL slices and values (owned by the Hessian)
     const int32_t* hwidth = nullptr;
     const double* hval = nullptr;
@@ -421,6 +425,7 @@ struct MembraneSolve {
     // the step's host side, made on first use: a pinned copy of scal, the event marking it filled, and
     // the stream the simulation steps on inside a batch
     double* hscal = nullptr;
+    uint64_t team_wait = ~uint64_t(0);  // ticks a team's wait may take (tests shorten it)
     hipEvent_t ready = nullptr;
     hipStream_t lane = nullptr;
     // device memory held by the arrays above
@@ -431,7 +436,8 @@ struct MembraneSolve {
                          mptr.bytes(), slcol.bytes(), mlcol.bytes(), s2e.bytes(), brow.bytes(), btptr.bytes(), bttri.bytes(),
                          rest.bytes(), xtry.bytes(), ftry.bytes(), z.bytes(), p.bytes(), p2.bytes(), q.bytes(),
                          y.bytes(), r.bytes(), dinv.bytes(), part.bytes(), ff.bytes(), svalf.bytes(), mvalf.bytes(),
-                         ppart.bytes(), scal.bytes(), mepart.bytes(), fdesc.bytes(), items.bytes()})
+                         ppart.bytes(), scal.bytes(), mepart.bytes(), fdesc.bytes(), items.bytes(), tcol.bytes(),
+                         slots.bytes(), tpart ? tpart->bytes() : size_t(0)})
             n += v;
         return n;
     }
@@ -581,6 +587,17 @@ void launch_scatter_rows(const void* src, const int32_t* perm, void* dst, int64_
 void launch_assemble(shell_hessian_s& h, hipStream_t s);
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,
                   hipStream_t s);
+// rows per member of a mesh on its own; one member up to `alone` rows, then one per compute unit, of `least` rows
+int64_t team_rows(int64_t nv);
+int64_t team_rows_spread(int64_t nv, int64_t alone, int64_t least);
+// The part with members of R rows, or null where it does not fit: each member's halo (the columns of its rows
+// that are other members' rows, ascending; `lists` receives them), the rows that others read, and the pairs'
+// local columns.  real: bytes of a direction's component in LDS.  row2, col2: a second pattern (CSR) whose
+// columns the members read too.  Synchronises s.
+std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, size_t real, hipStream_t s,
+                                     const std::vector<int64_t>* row2 = nullptr,
+                                     const std::vector<int32_t>* col2 = nullptr,
+                                     std::vector<std::vector<int32_t>>* lists = nullptr);
 // the layout of team solves (h.parts stays empty where a team cannot take the mesh); synchronises s
 void build_team(shell_hessian_s& h, hipStream_t s);
 // the part whose members hold at least `rows` rows (0: the simulation's own), or null; may synchronise s

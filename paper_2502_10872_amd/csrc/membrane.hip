@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <coroutine>
+#include <cstring>
 #include <exception>
 #include <thread>
 #include <utility>
@@ -134,11 +135,12 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
 constexpr int kMsBlk = 256;
 // device scalars
 enum : int { S_RZ, S_RZN, S_PQ, S_RR, S_RR0, S_TOL2, S_ALPHA, S_BETA, S_GSQ, S_SLOPE, S_E, S_IT, S_TARGET,
-             S_ACTIVE, S_REPLAY, S_BUDGET, S_YMAX, S_FRESH, S_COUNT };
+             S_ACTIVE, S_REPLAY, S_BUDGET, S_YMAX, S_FRESH, S_GONE, S_SAMPLE0, S_SAMPLE1, S_SAMPLES, S_COUNT };
 // The coupled PCG's state lives in two sets of these scalars (set k at scal + k S_COUNT) that alternate
 // with the direction buffers: a product reads its iteration's state from one set and stores the next into
 // the other, which no work-group of the same launch reads.  The solve's constants (S_TOL2, S_TARGET,
-// S_REPLAY, S_RR0) and the step's other scalars stay in set 0; the one-work-group solver uses set 0 only.
+// S_REPLAY, S_RR0) and the step's other scalars stay in set 0; the one-work-group solver and the team solve use
+// set 0 only.  S_GONE (an int) is the team's flag, S_SAMPLE* its sampled phases.
 
 template <int NQ>
 __device__ __forceinline__ void ms_partials(double (&v)[NQ], double* part, long ngroups) {
@@ -885,6 +887,12 @@ __global__ __launch_bounds__(kMsBlk) void ms_fin_max(const double* __restrict__ 
 
 }  // namespace
 
+}  // namespace shell
+
+#include "team_membrane.hpp"
+
+namespace shell {
+
 MembraneSolve::~MembraneSolve() {
     RuntimeLock lk(runtime_mutex());
     for (auto& g : graphs) (void)hipGraphExecDestroy(g.ex);
@@ -1008,11 +1016,19 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
     ms->mrow.upload(mrow.data(), mrow.size(), s);
     ms->mcol.alloc(std::max<size_t>(mcol.size(), 1));
     ms->mcol.upload(mcol.data(), mcol.size(), s);
+    // the deal of the rows for the team solve (its members read K_s's columns and the blocks')
+    std::vector<std::vector<int32_t>> halo;
+    // rows per member: one member up to 512, then as many members as compute units, of at least 256 rows (an
+    // iteration reads four times the matrix of the bending solve, so the rows are dealt out sooner: 65536 rows 15.6
+    // us with 256, 16.2 with 512; 128 rows gain 8% at 1089 and lose 10% at 16384)
+    const int64_t R = nv > 0 ? team_rows_spread(nv, 512, 256) : 0;
+    if ((st.cfg_flags & SHELL_FLAG_DIRECT_PRODUCT) == 0 && nv > 0)
+        ms->tpart = build_part(h, R, sizeof(double), s, &mrow, &mcol, &halo);
     // where each block is stored: CSR order (the direct product), or SELL-64 slices for the staged one
     const int64_t nnz_m = int64_t(mcol.size());
     std::vector<int64_t> mbase(size_t(std::max<int64_t>(nnz_m, 1)), 0);
     int64_t nblock_vals = 9 * nnz_m;
-    ms->staged = (st.cfg_flags & SHELL_FLAG_DIRECT_PRODUCT) == 0 && nv >= kMsStagedMinRows;
+    ms->staged = (st.cfg_flags & SHELL_FLAG_DIRECT_PRODUCT) == 0 && (nv >= kMsStagedMinRows || ms->tpart);
     if (ms->staged) {
         // each row group's distinct columns of K_s and of the blocks, with its own rows
         const int64_t G = ms_group_rows(nv);
@@ -1058,6 +1074,13 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
             const int64_t mslots = mptr[size_t(nsl)];
             std::vector<uint16_t> mlcol(size_t(mslots), 0);
             std::vector<int64_t> s2e(size_t(mslots), -1);
+            std::vector<uint16_t> tcol(ms->tpart ? size_t(mslots) : 0, 0);
+            auto team_local = [&](int64_t i, int32_t c) {  // column c as an id of the member that owns row i
+                const int64_t m = i / R, lo = m * R;
+                if (c >= lo && c < lo + R) return uint16_t(c - lo);
+                const auto& v = halo[size_t(m)];
+                return uint16_t(R + (std::lower_bound(v.begin(), v.end(), c) - v.begin()));
+            };
             for (int64_t sl = 0; sl < nsl; ++sl)
                 for (int lane = 0; lane < 64; ++lane) {
                     const int64_t i = 64 * sl + lane, g = i / G;
@@ -1069,7 +1092,9 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
                             mbase[size_t(e)] = slot;
                             s2e[size_t(slot)] = e;
                             mlcol[size_t(slot)] = local(g, mcol[size_t(e)]);
+                            if (ms->tpart) tcol[size_t(slot)] = team_local(i, mcol[size_t(e)]);
                         } else {
+                            if (ms->tpart) tcol[size_t(slot)] = uint16_t(i % R);  // zero value
                             mlcol[size_t(slot)] = i < nv ? local(g, int32_t(i)) : uint16_t(0);  // zero value
                         }
                     }
@@ -1097,10 +1122,16 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
             ms->mlcol.upload(mlcol.data(), mlcol.size(), s);
             ms->s2e.alloc(s2e.size());
             ms->s2e.upload(s2e.data(), s2e.size(), s);
+            if (ms->tpart) {
+                ms->tcol.alloc(tcol.size());
+                ms->tcol.upload(tcol.data(), tcol.size(), s);
+                ms->slots.alloc(team_slot_count(ms->tpart->members));
+            }
             SHELL_HIP(hipStreamSynchronize(s));  // the host copies are released on leaving the scope
         }
     }
     if (!ms->staged) {
+        ms->tpart.reset();
         ms->mstride = 1;
         for (int64_t e = 0; e < nnz_m; ++e) mbase[size_t(e)] = 9 * e;
     }
@@ -1367,6 +1398,76 @@ static void pcg_iterations(MembraneSolve& m, const double* mass, const uint8_t* 
 
 namespace {
 
+// Iterations of one launch at most (a launch of the largest meshes then takes some 0.5 s).
+constexpr int kMsTeamChunk = 4096;
+
+// One launch of the team solve of (M + dt^2 (K_s (x) I3 + K_m)) y = -g, or its continuation.
+void launch_team(shell_sim_s& sim, const double* mass, double dt2, double rtol2, int target, bool replay, bool resume,
+                 int limit, int every, hipStream_t s) {
+    MembraneSolve& m = *sim.ms;
+    const shell_hessian_s& h = *sim.h;
+    const TeamPart& tp = *m.tpart;
+    TeamMembraneArgs a{};
+    a.tptr = h.tptr.p;
+    a.twid = h.twid.p;
+    a.tval = m.mixed ? static_cast<const void*>(h.tvalf.p) : static_cast<const void*>(h.tval.p);
+    a.tcol = tp.col.p;
+    a.mptr = m.mptr.p;
+    a.mwidth = m.mwidth.p;
+    a.mval = m.mixed ? static_cast<const void*>(m.mvalf.p) : static_cast<const void*>(m.mval.p);
+    a.mcol = m.tcol.p;
+    a.mstride = long(m.mstride);
+    a.hptr = tp.hptr.p;
+    a.hcols = tp.hcols.p;
+    a.send = tp.send.p;
+    a.mass = mass;
+    a.kdiag = h.kdiag.p;
+    a.pinned = sim.pinned.p;
+    a.dinv = m.dinv.p;
+    a.g = sim.g.p;
+    a.r = m.r.p;
+    a.y = m.y.p;
+    a.p = m.p.p;
+    a.rows[0] = m.z.p;
+    a.rows[1] = m.p2.p;
+    a.slots = m.slots.p;
+    a.scal = m.scal.p;
+    a.nv = sim.nv;
+    a.dt2 = dt2;
+    a.rtol2 = rtol2;
+    a.R = tp.rows;
+    a.members = tp.members;
+    a.target = target;
+    a.replay = replay ? 1 : 0;
+    a.resume = resume ? 1 : 0;
+    a.limit = limit;
+    a.every = every;
+    a.wait = std::min(m.team_wait, kTeamWaitTicks);
+    m.pswap = false;  // the state is in set 0
+    ms_team_clear<<<1, kTeamThreads, 0, s>>>(m.slots.p, m.scal.p, tp.members);
+    const size_t lds = team_membrane_lds(tp.rows, tp.max_halo);
+    auto go = [&](auto f64, auto f32) {
+        if (m.mixed)
+            f32<<<unsigned(tp.members), kTeamThreads, lds, s>>>(a);
+        else
+            f64<<<unsigned(tp.members), kTeamThreads, lds, s>>>(a);
+    };
+    const int rpl = (tp.rows + kTeamThreads - 1) / kTeamThreads;
+    if (rpl <= 1) go(ms_team_pcg<double, 1>, ms_team_pcg<float, 1>);
+    else if (rpl <= 2) go(ms_team_pcg<double, 2>, ms_team_pcg<float, 2>);
+    else if (rpl <= 4) go(ms_team_pcg<double, 4>, ms_team_pcg<float, 4>);
+    else if (rpl <= 6) go(ms_team_pcg<double, 6>, ms_team_pcg<float, 6>);
+    else go(ms_team_pcg<double, 8>, ms_team_pcg<float, 8>);
+    SHELL_HIP(hipGetLastError());
+}
+
+// whether a member of the last launch gave up waiting, from the fetched scalars
+bool team_gone(const double* hs) {
+    int f;
+    std::memcpy(&f, hs + S_GONE, sizeof(f));
+    return f != 0;
+}
+
 // The host side of one simulation's step as a resumable task.  It suspends wherever it needs a value its
 // stream has yet to produce, leaving the event that marks the value ready, so that one host thread can
 // keep the steps of several simulations in flight on their own streams.
@@ -1406,6 +1507,13 @@ struct DeviceReady {
     hipEvent_t ev;
     bool await_ready() const noexcept { return false; }
     void await_suspend(StepTask::Handle h) const noexcept { h.promise().wait = ev; }
+    void await_resume() const noexcept {}
+};
+
+// co_await Later{}: suspend until the driver comes round again (what the step waits for is no event)
+struct Later {
+    bool await_ready() const noexcept { return false; }
+    void await_suspend(StepTask::Handle h) const noexcept { h.promise().wait = nullptr; }
     void await_resume() const noexcept {}
 };
 
@@ -1474,19 +1582,35 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
         }
         // the membrane tangent and the Jacobi preconditioner
         tangent_at(sim, sim.x.p, sim.mass.p, dt2, s);
-        // one PCG over all coordinates
+        // one PCG over all coordinates: by a team, launched once all its members' compute units are free, or
+        // (no team, or a member gave up waiting) as a chain of kernels
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
-        m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction
-        ms_pcg_init<<<ms_grid(nv), kMsBlk, 0, s>>>(sim.g.p, m.dinv.p, m.r.p, m.z.p, m.p.p, m.y.p, nv, part, ng);
-        ms_fin_init<<<1, kMsBlk, 0, s>>>(part, ng, m.scal.p, p.pcg_rtol * p.pcg_rtol, target, replay ? 1 : 0);
-        SHELL_HIP(hipGetLastError());
-        co_await fetch();
-        int chunk = 16;
-        while (pcg()[S_ACTIVE] != 0.0) {
-            pcg_iterations(m, sim.mass.p, sim.pinned.p, nv, dt2, chunk, graphs, s);
+        bool solved = false;
+        if (m.tpart) {
+            const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
+            TeamSlots& cu = TeamSlots::of_current_device();
+            for (bool resume = false; !solved; resume = true) {
+                TeamLease lease;
+                while (!lease.try_take(cu, m.tpart->members)) co_await Later{};
+                launch_team(sim, sim.mass.p, dt2, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
+                co_await fetch();
+                if (team_gone(hs)) break;
+                solved = pcg()[S_ACTIVE] == 0.0;
+            }
+        }
+        if (!solved) {
+            m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction
+            ms_pcg_init<<<ms_grid(nv), kMsBlk, 0, s>>>(sim.g.p, m.dinv.p, m.r.p, m.z.p, m.p.p, m.y.p, nv, part, ng);
+            ms_fin_init<<<1, kMsBlk, 0, s>>>(part, ng, m.scal.p, p.pcg_rtol * p.pcg_rtol, target, replay ? 1 : 0);
             SHELL_HIP(hipGetLastError());
             co_await fetch();
-            chunk = std::min(2 * chunk, 256);
+            int chunk = 16;
+            while (pcg()[S_ACTIVE] != 0.0) {
+                pcg_iterations(m, sim.mass.p, sim.pinned.p, nv, dt2, chunk, graphs, s);
+                SHELL_HIP(hipGetLastError());
+                co_await fetch();
+                chunk = std::min(2 * chunk, 256);
+            }
         }
         if (pcg()[S_BUDGET] == 2.0) {
             nonfinite = true;
@@ -1548,7 +1672,10 @@ struct LaneDrain {
 shell_status_t membrane_step(shell_sim_s& sim, const shell_step_params_t& p, shell_step_stats_t& out,
                              hipStream_t s) {
     StepTask t = membrane_step_task(sim, p, out, s);
-    while (!t.advance()) SHELL_HIP(hipStreamSynchronize(s));
+    while (!t.advance()) {
+        SHELL_HIP(hipStreamSynchronize(s));
+        if (!t.waiting_on()) std::this_thread::yield();
+    }
     return t.result();
 }
 
@@ -1607,7 +1734,7 @@ shell_status_t membrane_batch_step(shell_batch_s& b, const shell_step_params_t* 
                     --left;
                     merge(tasks[i].result());
                 }
-                moved = true;
+                moved = moved || done[i] || tasks[i].waiting_on();
             }
             // nothing has landed: poll again (blocking on one member would hold back the others whose
             // values land first; polling measured 4-8% faster on 32 simulations)
@@ -1668,17 +1795,30 @@ shell_status_t membrane_static(shell_sim_s& sim, const shell_step_params_t& p, c
         }
         tangent_at(sim, sim.x.p, sim.zmass.p, 1.0, s);
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
-        m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction
-        ms_pcg_init<<<ms_grid(nv), kMsBlk, 0, s>>>(sim.g.p, m.dinv.p, m.r.p, m.z.p, m.p.p, m.y.p, nv, part, ng);
-        ms_fin_init<<<1, kMsBlk, 0, s>>>(part, ng, m.scal.p, p.pcg_rtol * p.pcg_rtol, target, replay ? 1 : 0);
-        SHELL_HIP(hipGetLastError());
-        read_scal();
-        int chunk = 16;
-        while (pcg()[S_ACTIVE] != 0.0) {
-            pcg_iterations(m, sim.zmass.p, sim.pinned.p, nv, 1.0, chunk, graphs, s);
+        bool solved = false;
+        if (m.tpart) {
+            const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
+            for (bool resume = false; !solved; resume = true) {
+                TeamLease lease(TeamSlots::of_current_device(), m.tpart->members);
+                launch_team(sim, sim.zmass.p, 1.0, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
+                read_scal();
+                if (team_gone(hs)) break;
+                solved = pcg()[S_ACTIVE] == 0.0;
+            }
+        }
+        if (!solved) {
+            m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction
+            ms_pcg_init<<<ms_grid(nv), kMsBlk, 0, s>>>(sim.g.p, m.dinv.p, m.r.p, m.z.p, m.p.p, m.y.p, nv, part, ng);
+            ms_fin_init<<<1, kMsBlk, 0, s>>>(part, ng, m.scal.p, p.pcg_rtol * p.pcg_rtol, target, replay ? 1 : 0);
             SHELL_HIP(hipGetLastError());
             read_scal();
-            chunk = std::min(2 * chunk, 256);
+            int chunk = 16;
+            while (pcg()[S_ACTIVE] != 0.0) {
+                pcg_iterations(m, sim.zmass.p, sim.pinned.p, nv, 1.0, chunk, graphs, s);
+                SHELL_HIP(hipGetLastError());
+                read_scal();
+                chunk = std::min(2 * chunk, 256);
+            }
         }
         if (pcg()[S_BUDGET] == 2.0) {
             nonfinite = true;
@@ -1733,6 +1873,25 @@ void membrane_time_kernels(shell_sim_s& sim, double dt, int reps, shell_kernel_t
     SHELL_HIP(hipEventRecord(e1, s));
     out.force_ms = elapsed();
     tangent_at(sim, sim.x.p, sim.mass.p, dt2, s);
+    if (m.tpart) {
+        // the step's solve is one kernel: its phases over `reps` iterations, from the kernel's own clock
+        SHELL_HIP(hipMemcpyAsync(sim.g.p, m.ftry.p, size_t(n3) * sizeof(double), hipMemcpyDeviceToDevice, s));
+        double hs[S_COUNT];
+        {
+            TeamLease lease(TeamSlots::of_current_device(), m.tpart->members);
+            launch_team(sim, sim.mass.p, dt2, 0.0, reps + 1, true, false, 1 << 30, 1, s);
+            SHELL_HIP(hipMemcpyAsync(hs, m.scal.p, sizeof(hs), hipMemcpyDeviceToHost, s));
+            SHELL_HIP(hipStreamSynchronize(s));
+        }
+        if (!team_gone(hs) && hs[S_SAMPLES] > 0.0) {
+            out.spmv_ms = hs[S_SAMPLE0] * 1e-5 / hs[S_SAMPLES];
+            out.update_ms = hs[S_SAMPLE1] * 1e-5 / hs[S_SAMPLES];
+            out.reps = reps;
+            SHELL_HIP(hipEventDestroy(e0));
+            SHELL_HIP(hipEventDestroy(e1));
+            return;
+        }
+    }
     ms_pcg_init<<<ms_grid(nv), kMsBlk, 0, s>>>(m.ftry.p, m.dinv.p, m.r.p, m.z.p, m.p.p, m.y.p, nv, m.part.p, ng);
     ms_fin_init<<<1, kMsBlk, 0, s>>>(m.part.p, ng, m.scal.p, 0.0, 1 << 30, 1);
     const unsigned ug = ms_update_grid(nv);

@@ -1027,6 +1027,7 @@ shell_status_t batch_step(shell_batch_s& b, const shell_step_params_t* p, int np
 // test hook: the ticks (10 ns) a team's wait of this simulation's own steps may take
 extern "C" void shell_test_team_wait(shell_sim_s* sim, uint64_t ticks) {
     if (sim && sim->solo) sim->solo->team_wait = ticks;
+    if (sim && sim->ms) sim->ms->team_wait = ticks;
 }
 
 void batch_time_kernels(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out, hipStream_t s) {

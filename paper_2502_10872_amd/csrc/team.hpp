@@ -212,6 +212,47 @@ __device__ __forceinline__ void team_clear(double* slots, int* flag, int members
     if (threadIdx.x == 0) agent_store(flag, 0);
 }
 
+constexpr int kTeamThreads = 512;  // of a member: two waves per SIMD, 256 registers each
+
+template <typename MR>
+struct Pair;
+template <>
+struct Pair<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+template <>
+struct Pair<float> {
+    typedef float type __attribute__((ext_vector_type(2)));
+};
+
+// An exchanged row's value as bits; `unset` is a NaN pattern that no value is published as.
+template <typename VR>
+struct Row;
+template <>
+struct Row<double> {
+    typedef unsigned long long bits_t;
+    static constexpr bits_t unset = kUnset;
+    __device__ __forceinline__ static bits_t bits(double v) {
+        return __builtin_isnan(v) ? kPlainNan : bits_t(__double_as_longlong(v));
+    }
+    __device__ __forceinline__ static double value(bits_t u) { return __longlong_as_double((long long)u); }
+};
+template <>
+struct Row<float> {
+    typedef unsigned bits_t;
+    static constexpr bits_t unset = 0x7fdeadbeu;
+    __device__ __forceinline__ static bits_t bits(float v) { return __builtin_isnan(v) ? 0x7fc00000u : __float_as_uint(v); }
+    __device__ __forceinline__ static float value(bits_t u) { return __uint_as_float(u); }
+};
+
+// The same value, unknown to the compiler: what is computed from it inside a loop is computed there, in place
+// of once before the loop with a register per row held through it.
+template <typename V>
+__device__ __forceinline__ V here(V v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // ------------------------------------------------------------------ admission (host)
 
 // Compute units free for resident teams on one device, one member per unit.  A launch takes its members'
@@ -236,6 +277,12 @@ struct TeamLease {
     int n = 0;
     TeamLease() = default;
     TeamLease(TeamSlots& s, int count) : slots(&s), n(count) { s.acquire(count); }
+    bool try_take(TeamSlots& s, int count) {
+        if (!s.try_acquire(count)) return false;
+        slots = &s;
+        n = count;
+        return true;
+    }
     TeamLease(const TeamLease&) = delete;
     TeamLease& operator=(const TeamLease&) = delete;
     ~TeamLease() {

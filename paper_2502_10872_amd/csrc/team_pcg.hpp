@@ -31,57 +31,16 @@ enum : int { kTeamFresh = 0, kTeamRefine = 1, kTeamResume = 2 };
 // A member runs 512 threads (two waves per SIMD, 256 registers each).  With up to 1024 rows it holds the first
 // kTeamPairs pairs of each row's entries in registers for the whole solve (nine pairs: the eighteen neighbours
 // of a regular triangle-model row), so that an iteration reads no matrix at all; with more it streams it in
-// batches of kTeamBatch pairs, the next batch requested while one is multiplied.
-constexpr int kTeamThreads = 512;
+// batches of kTeamBatch pairs.
 constexpr int kTeamPairs = 9;
 template <typename MR>
 constexpr int kTeamBatch = sizeof(MR) == 8 ? 3 : 9;
-
 
 // LDS of a member: the directions of its rows and its halo, and of its rows the diagonal (float64: m + dt^2 K_ii;
 // mixed: the mass and the Jacobi entry).
 template <typename VR>
 constexpr size_t team_lds(int rows, int halo) {
     return size_t(rows + halo) * 3 * sizeof(VR) + size_t(rows) * 8;
-}
-
-template <typename MR>
-struct Pair;
-template <>
-struct Pair<double> {
-    typedef double type __attribute__((ext_vector_type(2)));
-};
-template <>
-struct Pair<float> {
-    typedef float type __attribute__((ext_vector_type(2)));
-};
-
-// An exchanged row's value as bits; `unset` is a NaN pattern that no value is published as.
-template <typename VR>
-struct Row;
-template <>
-struct Row<double> {
-    typedef unsigned long long bits_t;
-    static constexpr bits_t unset = kUnset;
-    __device__ __forceinline__ static bits_t bits(double v) {
-        return __builtin_isnan(v) ? kPlainNan : bits_t(__double_as_longlong(v));
-    }
-    __device__ __forceinline__ static double value(bits_t u) { return __longlong_as_double((long long)u); }
-};
-template <>
-struct Row<float> {
-    typedef unsigned bits_t;
-    static constexpr bits_t unset = 0x7fdeadbeu;
-    __device__ __forceinline__ static bits_t bits(float v) { return __builtin_isnan(v) ? 0x7fc00000u : __float_as_uint(v); }
-    __device__ __forceinline__ static float value(bits_t u) { return __uint_as_float(u); }
-};
-
-// The same value, unknown to the compiler: what is computed from it inside a loop is computed there, in place
-// of once before the loop with a register per row held through it.
-template <typename V>
-__device__ __forceinline__ V here(V v) {
-    asm volatile("" : "+v"(v));
-    return v;
 }
 
 template <typename VR, typename MR, int RPL>

@@ -109,3 +109,48 @@ def test_a_member_that_gives_up_hands_the_solve_to_the_chain(precision):
         xc, vc, _ = _step(pb, mesh, x, v)
     assert np.array_equal(xa, xb) and np.array_equal(va, vb)
     assert rel(xc - mesh.X, xb - mesh.X) <= BOUND[precision] and rel(vc, vb) <= BOUND[precision]
+
+
+def _no_waiting(sim, ticks):
+    limit = S.lib().shell_test_team_wait
+    limit.argtypes, limit.restype = [ctypes.c_void_p, ctypes.c_uint64], None
+    limit(sim, ticks)
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("model,n", [("SS", 5), ("ES", 22), ("SS", 23), ("FS", 33), ("SS", 257), ("ES", 420), ("SS", 600),
+                                     ("FS", 850)])
+def test_membrane_team_solves_equal_the_kernel_chain(model, n, precision):
+    """The coupled solve with the membrane, as a team and (no time to wait; a mesh of one member never waits, so
+    its two runs are one) as a chain: one member up to 512 rows, members of 256 rows, then one per compute unit.
+    Single coordinates held as well as the ends."""
+    mesh = I.workload_cylinder(n, model)
+    x, v = _start(mesh)
+    counts = np.zeros((2, 3), np.int32)
+    counts[:, 0] = 20
+    params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=0.0, replay=counts)
+    out = []
+    held = np.arange(mesh.nv) % 5 * (np.arange(mesh.nv) % 11 == 0)
+    with S.Problem(mesh, MAT, precision=precision, flags=S.SHELL_FLAG_MEMBRANE, held=held) as pb:
+        for ticks in (2 ** 64 - 1, 0):
+            _no_waiting(pb.sim, ticks)
+            S.shell_sim_set_state(pb.sim, x, v, 0)
+            S.shell_step_implicit(pb.sim, params)
+            out.append(S.shell_sim_get_state(pb.sim, mesh.nv)[:2])
+    (xa, va), (xb, vb) = out
+    bound = 1e-10 if precision == S.SHELL_PREC_FP64 else 1e-6
+    assert rel(xa - mesh.X, xb - mesh.X) <= bound and rel(va, vb) <= bound
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+def test_a_membrane_solve_over_several_launches_is_the_same_solve(precision):
+    mesh = I.workload_cylinder(40, "SS")
+    x, v = _start(mesh)
+    out = []
+    with S.Problem(mesh, MAT, precision=precision, flags=S.SHELL_FLAG_MEMBRANE) as pb:
+        for chunk in (0, 7):
+            params, _keep = S.step_params(1 / 60, max_newton=2, pcg_rtol=1e-8, chunk=chunk)
+            S.shell_sim_set_state(pb.sim, x, v, 0)
+            rc, st = S.shell_step_implicit(pb.sim, params)
+            out.append((st["counts"], *S.shell_sim_get_state(pb.sim, mesh.nv)[:2]))
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
