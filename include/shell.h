@@ -75,7 +75,9 @@ typedef struct {
 
 typedef struct {
     int32_t precision;       /* shell_precision_t */
-    int32_t block_vertices;  /* vertices per force work-group tile, 64..4096; 0 selects the default (2048) */
+    int32_t block_vertices;  /* vertices per force work-group tile, 64..4096; 0 selects the default: vertices
+                                ordered in tiles of 2048, and 2048 or fewer per work-group (at least 128) so
+                                that a mesh fills the chip */
     int32_t reorder;         /* internal vertex order: 1 (default) recursive coordinate bisection into compact
                                 tiles of block_vertices, 2 Morton order, 0 the caller's order */
     int32_t flags;           /* 0, or SHELL_FLAG_DIRECT_PRODUCT, SHELL_FLAG_WORLD_FRAME, SHELL_FLAG_MEMBRANE */
@@ -161,7 +163,7 @@ typedef struct {
     int64_t nv, nt;
     int64_t ns;             /* unique stencils */
     int64_t ns_tiled;       /* stencil copies in the tiled force layout (halo stencils repeat) */
-    int64_t nblocks;        /* force work-group tiles */
+    int64_t nblocks;        /* force work-group tiles, of block_vertices vertices */
     int32_t model, k, r, precision;
     int32_t block_vertices;
     int32_t reserved;

@@ -67,6 +67,18 @@ void check_params(const shell_step_params_t& p) {
             SHELL_CHECK(p.replay_counts[q] >= 0, SHELL_E_INVALID_ARG, "negative replay count");
 }
 
+// Vertices per force work-group when the caller leaves the choice: the vertices are ordered in tiles of `order`
+// (2048); a work-group takes a power of two of them, at least 128, that makes at most 512 work-groups (two per
+// CU), so that meshes of all sizes fill the chip: at 2048 a mesh of 65536 vertices kept 32 of 256 CUs busy.
+// More, smaller work-groups only repeat more boundary stencils.  shell_eval_forces at 65536 vertices, 2048, 512,
+// 256, 128 and 64 vertices: ES with membrane FP64 60.4, 28.0, 22.8, 23.4, 30.1 us, SS mixed 34.9, 18.4, 16.2,
+// 15.7, 19.8; at 262144, 2048, 512 and 128: SS FP64 55.2, 43.2, 52.0; at 524176, 2048 and 512: 72.5, 74.7.
+int force_tile_vertices(int64_t nv, int order) {
+    int t = 128;
+    while (t < order && nv > int64_t(512) * t) t *= 2;
+    return t;
+}
+
 __global__ void gather1(const double* __restrict__ src, const int32_t* __restrict__ perm, double* __restrict__ dst,
                         long n) {
     long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
@@ -134,7 +146,7 @@ shell_status_t shell_build_stencils(const double* X, int64_t nv, const int32_t* 
         st->precision = precision;
         st->nv = nv;
         st->nt = nt;
-        st->T = T;
+        st->T = (cfg && cfg->block_vertices > 0) ? T : force_tile_vertices(nv, T);
         st->cfg_flags = cfg_flags;
         st->young = mat->young;
         st->poisson = mat->poisson;
@@ -217,7 +229,7 @@ shell_status_t shell_build_stencils(const double* X, int64_t nv, const int32_t* 
             SHELL_CHECK(flags[q] == 0, SHELL_E_DEGENERATE,
                         "degenerate stencil (zero area or height, or ill-conditioned quadratic fit)");
         // tiles for the force kernel
-        Tiling til = build_tiling(st->h_idx, k, st->ns, nv, T);
+        Tiling til = build_tiling(st->h_idx, k, st->ns, nv, st->T);
         st->nblocks = til.nblocks;
         st->ns_tiled = til.count;
         st->nst_pad = int64_t(til.src.size());

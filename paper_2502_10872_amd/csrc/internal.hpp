@@ -276,7 +276,7 @@ struct shell_stencils_s {
     int model = 0, k = 4, r = 1, precision = 0;
     int64_t nv = 0, nt = 0, ns = 0, ns_tiled = 0, nblocks = 0;
     int64_t nst_pad = 0;  // tiled list length with the per-tile alignment padding
-    int T = 1024;
+    int T = 1024;  // vertices per force work-group
     int cfg_flags = 0;  // SHELL_FLAG_*
     bool reordered = false;
     double young = 0, poisson = 0, thickness = 0, density = 0, kb = 0;

@@ -1,0 +1,50 @@
+"""The default size of a force work-group's vertex tile against tiles of 2048 vertices set by the caller.
+
+The default orders the vertices in tiles of 2048 too, so the two share the vertex order; the fixed-point
+accumulation adds the same integers per vertex whatever the tile, so the forces agree bit for bit.  The energy
+is summed per tile in float64: with E the sum of some 1e5 terms of one sign the two groupings differ by less
+than 1e-12 of it."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_10872_amd import inputs as I
+from paper_2502_10872_amd import shell as S
+
+pytestmark = pytest.mark.gpu
+
+
+def eval_forces(mesh, x, model, precision, block, flags):
+    with S.Problem(mesh, I.MATERIAL, model=model, precision=precision, block_vertices=block, flags=flags,
+                   sim=False) as pb:
+        xd = torch.as_tensor(x, device="cuda")
+        f = torch.full((mesh.nv, 3), float("nan"), device="cuda",
+                       dtype=torch.float32 if precision == S.SHELL_PREC_MIXED else torch.float64)
+        e = torch.zeros(1, device="cuda", dtype=torch.float64)
+        out = []
+        for call in (S.shell_eval_forces, S.shell_eval_forces_noalloc):
+            f.fill_(float("nan"))
+            call(pb.st, xd, f, e)
+            torch.cuda.synchronize()
+            out.append((f.cpu().numpy(), float(e.item())))
+        return out, pb.info
+
+
+# one tile; the last vertex alone in its tile; either side of the first change of size (512 tiles of 128);
+# tiles of 512; the largest mesh below whole ordering tiles
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("model,n,block,flags", [
+    ("EP", 5, 128, 0), ("FP", 23, 128, 0), ("SS", 43, 128, S.SHELL_FLAG_MEMBRANE), ("ES", 256, 128, 0),
+    ("FS", 257, 256, S.SHELL_FLAG_MEMBRANE), ("SP", 512, 512, 0), ("ES", 700, 1024, S.SHELL_FLAG_MEMBRANE),
+    ("SS", 725, 2048, 0)])
+def test_default_tiles_give_the_forces_of_whole_ordering_tiles(model, n, block, flags, precision):
+    mesh = I.plate_mesh(n, 1.0, 0.2, 7, model) if model.endswith("P") else I.workload_sphere_cap(n, model)
+    x = mesh.X + 1e-3 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
+    got, info = eval_forces(mesh, x, model, precision, 0, flags)
+    want, winfo = eval_forces(mesh, x, model, precision, 2048, flags)
+    assert info["block_vertices"] == block and info["nblocks"] == -(-mesh.nv // block)
+    assert winfo["block_vertices"] == 2048
+    for (f, e), (fw, ew) in zip(got, want):
+        assert np.array_equal(f, fw)
+        assert abs(e - ew) <= 1e-12 * abs(ew)
