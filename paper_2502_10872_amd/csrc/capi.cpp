@@ -7,6 +7,7 @@
 #include <mutex>
 #include <new>
 
+#include "devmath.hpp"
 #include "internal.hpp"
 
 using namespace shell;
@@ -302,53 +303,90 @@ shell_status_t shell_stencils_export(shell_stencils_t st, int32_t* idx, double* 
     });
 }
 
+namespace {
+
+// the descriptor of a force evaluation from and into the caller's order
+ForceDesc caller_desc(const shell_stencils_s& st, const double* xin, void* fout, double* epart) {
+    ForceDesc d{};
+    d.x = xin;
+    d.X = st.X.p;
+    d.f = fout;
+    d.epart = epart;
+    d.bias = st.bias.p;
+    d.boff = st.boff.p;
+    d.tidx = st.tidx.p;
+    d.trec = st.precision == SHELL_PREC_MIXED ? static_cast<const void*>(st.trec32.p)
+                                              : static_cast<const void*>(st.trec64.p);
+    d.nst = st.nst_pad;
+    d.nv = st.nv;
+    d.T = st.T;
+    d.model = st.model;
+    d.kb = st.kb;
+    d.fscale = st.fscale;
+    d.nu = st.poisson;
+    return d;
+}
+
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const auto p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + nb && q < p + na;
+}
+
+// Forces from and into the caller's order.  The kernels read positions and write forces through the permutation
+// themselves: gather, scatter and energy kernels around them made 15 us of launches at any small size (now 7-8 us)
+// and passes over memory at the large ones (1M vertices, SS mixed 89.6 -> 79.8 us, SS FP64 129.5 -> 111.8; 142K, ES with membrane FP64 39.6 -> 36.5).
+// Where f overlaps x the positions are gathered first, since a tile's forces go out while others still read.
+void launch_caller_forces(shell_stencils_s& st, const double* x, void* f, double* energy, double* xin, void* fout,
+                          double* epart, const ForceDesc* desc, const WorkItem* items, uint32_t* arrived,
+                          hipStream_t s) {
+    const bool membrane = (st.cfg_flags & SHELL_FLAG_MEMBRANE) != 0;
+    const size_t n3 = size_t(3 * st.nv);
+    const size_t real = st.precision == SHELL_PREC_MIXED ? sizeof(float) : sizeof(double);
+    ForceCaller in;
+    in.perm = st.perm_d.p;
+    if (overlap(x, n3 * sizeof(double), f, n3 * real))
+        launch_gather_rows(x, st.perm_d.p, xin, st.nv, s);
+    else
+        in.x = x;
+    ForceCaller all = in;
+    all.f = f;
+    all.energy = energy;
+    all.arrived = arrived;
+    all.add = st.bias_e0;
+    launch_force_items(st.model, st.precision, desc, items, st.nblocks, st.T, s, nullptr, nullptr,
+                       membrane ? in : all);
+    if (membrane) launch_membrane_forces(st, xin, fout, s, nullptr, all, epart);
+}
+
+}  // namespace
+
 shell_status_t shell_eval_forces(shell_stencils_t st, const double* x, void* f, double* energy,
                                  shell_stream_t stream) {
     return guarded([&]() -> shell_status_t {
         SHELL_CHECK(st && (x || st->nv == 0) && (f || st->nv == 0), SHELL_E_INVALID_ARG, "null argument");
         hipStream_t s = as_stream(stream);
-        const bool f32 = st->precision == SHELL_PREC_MIXED;
-        if (st->nv > 0 && !st->fdesc.p) {
-            // caller-order staging, descriptor and tile items, made on first use
+        if (st->nv == 0) {
+            if (energy) launch_zero_energy(energy, s);  // a kernel, not a memset node
+            return SHELL_OK;
+        }
+        if (!st->fdesc.p) {
+            // staging, descriptor and tile items, made on first use
+            if (st->cfg_flags & SHELL_FLAG_MEMBRANE) st->fout.alloc(size_t(3 * st->nv));
             st->xin.alloc(size_t(3 * st->nv));
-            st->fout.alloc(size_t(3 * st->nv));
-            ForceDesc d{};
-            d.x = st->xin.p;
-            d.X = st->X.p;
-            d.f = st->fout.p;
-            d.epart = st->epart.p;
-            d.bias = st->bias.p;
-            d.boff = st->boff.p;
-            d.tidx = st->tidx.p;
-            d.trec = f32 ? static_cast<const void*>(st->trec32.p) : static_cast<const void*>(st->trec64.p);
-            d.nst = st->nst_pad;
-            d.nv = st->nv;
-            d.T = st->T;
-            d.model = st->model;
-            d.kb = st->kb;
-            d.fscale = st->fscale;
-            d.nu = st->poisson;
+            const ForceDesc d = caller_desc(*st, st->xin.p, st->fout.p, st->epart.p);
             std::vector<WorkItem> items(size_t(st->nblocks));
             for (int64_t t = 0; t < st->nblocks; ++t) items[size_t(t)] = {0, int32_t(t)};
             st->fdesc.alloc(1);
             st->tile_items.alloc(items.size());
+            const std::vector<uint32_t> zeros(arrival_counters(st->nblocks), 0u);
+            st->arrived.alloc(zeros.size());
+            st->arrived.upload(zeros.data(), zeros.size(), s);
             st->fdesc.upload(&d, 1, s);
             st->tile_items.upload(items.data(), items.size(), s);
             SHELL_HIP(hipStreamSynchronize(s));
         }
-        if (st->nv > 0) {
-            launch_gather_rows(x, st->perm_d.p, st->xin.p, st->nv, s);
-            launch_force_items(st->model, st->precision, st->fdesc.p, st->tile_items.p, st->nblocks, st->T, s);
-            if (st->cfg_flags & SHELL_FLAG_MEMBRANE) launch_membrane_forces(*st, st->xin.p, st->fout.p, s);
-            launch_scatter_rows(st->fout.p, st->perm_d.p, f, st->nv, f32, s);
-        }
-        if (energy) {
-            if (st->nv == 0)
-                launch_energy_finalize(nullptr, 0, 0.0, energy, s);  // a kernel, not a memset node
-            else
-                launch_energy_finalize(st->epart.p, st->nblocks, st->bias_e0, energy, s, st->mepart.p,
-                                       int64_t(st->mepart.n));
-        }
+        launch_caller_forces(*st, x, f, energy, st->xin.p, st->fout.p, st->epart.p, st->fdesc.p, st->tile_items.p,
+                             st->arrived.p, s);
         return SHELL_OK;
     });
 }
@@ -362,7 +400,10 @@ namespace {
 // partials, the force descriptor and the tile work items.  The array's name is a host-side stand-in:
 // host code uses only the device address hipGetSymbolAddress returns for the current device.
 constexpr size_t kScratchBytes = size_t(64) << 20;
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+// after them the arrival counters of the energy sum: 128 bytes per 16 tiles (at least 64 vertices each), less than
+// 176 KiB for the largest mesh that the rest holds
+constexpr size_t kScratchCounters = size_t(256) << 10;
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchCounters];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -391,7 +432,6 @@ shell_status_t shell_eval_forces_noalloc(shell_stencils_t st, const double* x, v
     return guarded([&]() -> shell_status_t {
         SHELL_CHECK(st && (x || st->nv == 0) && (f || st->nv == 0), SHELL_E_INVALID_ARG, "null argument");
         hipStream_t s = as_stream(stream);
-        const bool f32 = st->precision == SHELL_PREC_MIXED;
         // layout of the scratch: positions, force, energy partials, descriptor, tile items
         const size_t o_x = 0, o_f = align256(o_x + size_t(3 * st->nv) * sizeof(double));
         const size_t o_e = align256(o_f + size_t(3 * st->nv) * sizeof(double));
@@ -402,7 +442,7 @@ shell_status_t shell_eval_forces_noalloc(shell_stencils_t st, const double* x, v
                     "mesh too large for the no-allocation force entry point (its 64 MiB scratch holds about "
                     "1.39 million vertices)");
         if (st->nv == 0) {
-            if (energy) launch_energy_finalize(nullptr, 0, 0.0, energy, s);
+            if (energy) launch_zero_energy(energy, s);
             return SHELL_OK;
         }
         unsigned char* base = static_cast<unsigned char*>(scratch_for_current_device());
@@ -411,30 +451,12 @@ shell_status_t shell_eval_forces_noalloc(shell_stencils_t st, const double* x, v
         double* epart = reinterpret_cast<double*>(base + o_e);
         ForceDesc* desc = reinterpret_cast<ForceDesc*>(base + o_d);
         WorkItem* items = reinterpret_cast<WorkItem*>(base + o_i);
-        ForceDesc d{};
-        d.x = xin;
-        d.X = st->X.p;
-        d.f = fout;
-        d.epart = epart;
-        d.bias = st->bias.p;
-        d.boff = st->boff.p;
-        d.tidx = st->tidx.p;
-        d.trec = f32 ? static_cast<const void*>(st->trec32.p) : static_cast<const void*>(st->trec64.p);
-        d.nst = st->nst_pad;
-        d.nv = st->nv;
-        d.T = st->T;
-        d.model = st->model;
-        d.kb = st->kb;
-        d.fscale = st->fscale;
-        d.nu = st->poisson;
+        uint32_t* arrived = reinterpret_cast<uint32_t*>(base + kScratchBytes);
+        SHELL_CHECK(arrival_counters(st->nblocks) * sizeof(uint32_t) <= kScratchCounters, SHELL_E_INVALID_ARG,
+                    "too many tiles for the no-allocation force entry point");
         // descriptor and items written by kernels on the stream (no host-to-device copy to order)
-        launch_write_force_desc(d, desc, items, st->nblocks, s);
-        launch_gather_rows(x, st->perm_d.p, xin, st->nv, s);
-        launch_force_items(st->model, st->precision, desc, items, st->nblocks, st->T, s);
-        if (st->cfg_flags & SHELL_FLAG_MEMBRANE) launch_membrane_forces(*st, xin, fout, s);
-        launch_scatter_rows(fout, st->perm_d.p, f, st->nv, f32, s);
-        if (energy)
-            launch_energy_finalize(epart, st->nblocks, st->bias_e0, energy, s, st->mepart.p, int64_t(st->mepart.n));
+        launch_write_force_desc(caller_desc(*st, xin, fout, epart), desc, items, arrived, st->nblocks, s);
+        launch_caller_forces(*st, x, f, energy, xin, fout, epart, desc, items, arrived, s);
         return SHELL_OK;
     });
 }
@@ -896,7 +918,7 @@ shell_status_t shell_sim_device_bytes(shell_sim_t sim, int64_t* stencil_bytes, i
         for (size_t v : {st.X.bytes(), st.tris.bytes(), st.perm_d.bytes(), st.idx.bytes(), st.B.bytes(),
                          st.k0.bytes(), st.flags.bytes(), st.boff.bytes(), st.tsrc.bytes(), st.tidx.bytes(),
                          st.trec64.bytes(), st.trec32.bytes(), st.xin.bytes(),
-                         st.fout.bytes(), st.epart.bytes(), st.fdesc.bytes(), st.tile_items.bytes(), st.bias.bytes(),
+                         st.fout.bytes(), st.epart.bytes(), st.fdesc.bytes(), st.tile_items.bytes(), st.arrived.bytes(), st.bias.bytes(),
                          st.mtid.bytes(), st.mtrest.bytes(), st.mboff.bytes(), st.mepart.bytes()})
             a += int64_t(v);
         for (size_t v : {h.scol.bytes(), h.width.bytes(), h.sptr.bytes(), h.rowlen.bytes(), h.val.bytes(),

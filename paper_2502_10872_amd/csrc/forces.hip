@@ -215,7 +215,8 @@ constexpr int kMaxForceThreads = 1024;
 // One work-group per (mesh, vertex tile) work item.  K = 4 (edge) or 6 (triangle) vertices per stencil.
 template <int MODEL, typename R>
 __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc* __restrict__ descs,
-                                                   const WorkItem* __restrict__ items, long nitems) {
+                                                   const WorkItem* __restrict__ items, long nitems,
+                                                   ForceCaller caller) {
     constexpr bool EDGE = (MODEL == SHELL_EP || MODEL == SHELL_ES);
     constexpr bool SHELL = (MODEL == SHELL_ES || MODEL == SHELL_FS || MODEL == SHELL_SS);
     constexpr int K = EDGE ? 4 : 6;
@@ -229,7 +230,8 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
     const ForceDesc& d = descs[wi.mesh];
     // global-address views of the descriptor's pointers: global loads wait on the vector-memory counter
     // only, so the LDS accumulation does not stall behind loads in flight
-    const gbl<const double>* x = G(d.x);
+    const gbl<const double>* x = G(caller.x ? caller.x : d.x);
+    const gbl<const int32_t>* cperm = caller.x ? G(caller.perm) : nullptr;
     const gbl<const double>* X = G(d.X);
     const R kb = R(d.kb), nu = R(d.nu);
     const long blk = wi.unit;
@@ -324,8 +326,10 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
             for (int q = 0; q < NV; ++q) in.ob[q] = R(fv[q]);
         }
 #pragma unroll
-        for (int j = 0; j < K; ++j)
-            in.pg[j] = {x[3L * in.vid[j]], x[3L * in.vid[j] + 1], x[3L * in.vid[j] + 2]};
+        for (int j = 0; j < K; ++j) {
+            const long v = cperm ? cperm[in.vid[j]] : in.vid[j];
+            in.pg[j] = {x[3 * v], x[3 * v + 1], x[3 * v + 2]};
+        }
         if constexpr (REST) {
 #pragma unroll
             for (int j = 0; j < K; ++j)
@@ -492,8 +496,12 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
         compute(a);
     }
     __syncthreads();
-    gbl<R>* out = G(static_cast<R*>(d.f)) + 3 * base;
     const double sc = d.fscale;
+    gbl<R>* out = G(static_cast<R*>(caller.f ? caller.f : d.f));
+    const gbl<const int32_t>* perm = caller.f ? G(caller.perm) : nullptr;
+    auto at = [&](int i) {  // where component i of the tile goes
+        return perm ? 3L * perm[base + i / 3] + i % 3 : 3 * base + i;
+    };
     if constexpr (!MIX) {
         if (d.bias) {
             // plates with clamped edges: the constant force and energy terms that make the clamped
@@ -501,20 +509,24 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
             const gbl<const double>* b = G(d.bias) + 3 * base;
             for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) {
                 const double bi = b[i];
-                out[i] = acc.get(i) * sc + bi;
-                e_own -= bi * x[3 * base + i];
+                out[at(i)] = acc.get(i) * sc + bi;
+                e_own -= bi * x[cperm ? 3L * cperm[base + i / 3] + i % 3 : 3 * base + i];
             }
         } else {
-            for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[i] = R(acc.get(i) * sc);
+            for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[at(i)] = R(acc.get(i) * sc);
         }
     } else {
-        for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[i] = R(acc.get(i) * sc);
+        for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[at(i)] = R(acc.get(i) * sc);
     }
     if (d.epart) {
         __shared__ double sh[kMaxForceThreads / 64];
         double v[1] = {e_own};
         block_sum<1>(v, sh);
-        if (threadIdx.x == 0) d.epart[blk] = v[0];
+        if (!caller.energy) {
+            if (threadIdx.x == 0) d.epart[blk] = v[0];
+        } else if (last_block_sum(v[0], blk, nitems, d.epart, caller.arrived, sh)) {
+            if (threadIdx.x == 0) *caller.energy = v[0] + caller.add;
+        }
     }
 }
 
@@ -537,35 +549,28 @@ int force_threads(Kernel kernel) {
 
 template <int MODEL>
 void launch_model(int precision, const ForceDesc* descs, const WorkItem* items, long nitems, int lds_T,
-                  hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                  hipStream_t s, hipEvent_t start, hipEvent_t stop, const ForceCaller& caller) {
     static const int threads_d = force_threads(force_tiles<MODEL, double>);
     static const int threads_f = force_threads(force_tiles<MODEL, float>);
     const dim3 grid(unsigned(xcd_grid(nitems)));
     // start/stop (may be null) receive the dispatch's own begin and end times
     if (precision == SHELL_PREC_FP64)
         hipExtLaunchKernelGGL(force_tiles<MODEL, double>, grid, dim3(threads_d), uint32_t(TileAccT<2>::bytes(lds_T)),
-                              s, start, stop, 0, descs, items, nitems);
+                              s, start, stop, 0, descs, items, nitems, caller);
     else
         hipExtLaunchKernelGGL(force_tiles<MODEL, float>, grid, dim3(threads_f), uint32_t(TileAccT<1>::bytes(lds_T)),
-                              s, start, stop, 0, descs, items, nitems);
+                              s, start, stop, 0, descs, items, nitems, caller);
     SHELL_HIP(hipGetLastError());
 }
 
-__global__ void energy_finalize(const double* __restrict__ part, long n, double add, const double* __restrict__ extra,
-                                long m, double* __restrict__ out) {
-    __shared__ double sh[16];
-    double acc = 0.0;
-    for (long i = threadIdx.x; i < n; i += blockDim.x) acc += part[i];
-    for (long i = threadIdx.x; i < m; i += blockDim.x) acc += extra[i];
-    double v[1] = {acc};
-    block_sum<1>(v, sh);
-    if (threadIdx.x == 0) *out = v[0] + add;
-}
+__global__ void zero_energy(double* __restrict__ out) { *out = 0.0; }
 
-__global__ void write_force_desc(ForceDesc d, ForceDesc* __restrict__ dst, WorkItem* __restrict__ items, long n) {
+__global__ void write_force_desc(ForceDesc d, ForceDesc* __restrict__ dst, WorkItem* __restrict__ items,
+                                 uint32_t* __restrict__ arrived, long counters, long n) {
     const long t = blockIdx.x * long(blockDim.x) + threadIdx.x;
     if (t == 0) *dst = d;
     if (t < n) items[t] = WorkItem{0, int32_t(t)};
+    if (t < counters) arrived[t] = 0;
 }
 
 __global__ void gather_rows(const double* __restrict__ src, const int32_t* __restrict__ perm,
@@ -592,27 +597,28 @@ __global__ void scatter_rows(const T* __restrict__ src, const int32_t* __restric
 }  // namespace
 
 void launch_force_items(int model, int precision, const ForceDesc* descs, const WorkItem* items, long nitems,
-                        int lds_T, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                        int lds_T, hipStream_t s, hipEvent_t start, hipEvent_t stop, const ForceCaller& caller) {
     if (nitems <= 0) return;
     switch (model) {
-        case SHELL_EP: launch_model<SHELL_EP>(precision, descs, items, nitems, lds_T, s, start, stop); break;
-        case SHELL_ES: launch_model<SHELL_ES>(precision, descs, items, nitems, lds_T, s, start, stop); break;
-        case SHELL_FP: launch_model<SHELL_FP>(precision, descs, items, nitems, lds_T, s, start, stop); break;
-        case SHELL_FS: launch_model<SHELL_FS>(precision, descs, items, nitems, lds_T, s, start, stop); break;
-        case SHELL_SP: launch_model<SHELL_SP>(precision, descs, items, nitems, lds_T, s, start, stop); break;
-        case SHELL_SS: launch_model<SHELL_SS>(precision, descs, items, nitems, lds_T, s, start, stop); break;
+        case SHELL_EP: launch_model<SHELL_EP>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
+        case SHELL_ES: launch_model<SHELL_ES>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
+        case SHELL_FP: launch_model<SHELL_FP>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
+        case SHELL_FS: launch_model<SHELL_FS>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
+        case SHELL_SP: launch_model<SHELL_SP>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
+        case SHELL_SS: launch_model<SHELL_SS>(precision, descs, items, nitems, lds_T, s, start, stop, caller); break;
         default: throw Error(SHELL_E_INVALID_ARG, "unknown model");
     }
 }
 
-void launch_write_force_desc(const ForceDesc& d, ForceDesc* dst, WorkItem* items, int64_t ntiles, hipStream_t s) {
-    write_force_desc<<<unsigned((std::max<int64_t>(ntiles, 1) + 255) / 256), 256, 0, s>>>(d, dst, items, ntiles);
+void launch_write_force_desc(const ForceDesc& d, ForceDesc* dst, WorkItem* items, uint32_t* arrived, int64_t ntiles,
+                             hipStream_t s) {
+    const long counters = long(arrival_counters(ntiles)), n = std::max<long>(ntiles, counters);
+    write_force_desc<<<unsigned((n + 255) / 256), 256, 0, s>>>(d, dst, items, arrived, counters, ntiles);
     SHELL_HIP(hipGetLastError());
 }
 
-void launch_energy_finalize(const double* epart, int64_t n, double add, double* energy, hipStream_t s,
-                            const double* extra, int64_t m) {
-    energy_finalize<<<1, 256, 0, s>>>(epart, n, add, extra, m, energy);
+void launch_zero_energy(double* energy, hipStream_t s) {
+    zero_energy<<<1, 1, 0, s>>>(energy);
     SHELL_HIP(hipGetLastError());
 }
 

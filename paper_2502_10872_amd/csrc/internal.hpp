@@ -208,6 +208,16 @@ struct ForceDesc {
     double fscale;         // power-of-two force scale of the tile accumulation (TileAcc)
 };
 
+// Arrays in the caller's vertex order that a force kernel reads and writes itself (all null: internal order).
+struct ForceCaller {
+    const int32_t* perm = nullptr;  // internal id -> caller id
+    const double* x = nullptr;      // positions, or null: read the descriptor's (internal order)
+    void* f = nullptr;              // double or float forces, or null: write the descriptor's
+    double* energy = nullptr;       // the total, or null
+    uint32_t* arrived = nullptr;    // arrival counters of the sum (arrival_counters), at zero between calls
+    double add = 0.0;               // a constant part of the total
+};
+
 // Per-mesh arguments of the implicit-step kernels.
 struct PcgState {
     double rz[3], rr[3], tol2[3], alpha[3], beta[3];
@@ -318,6 +328,7 @@ struct shell_stencils_s {
     shell::DevArray<double> epart;       // [nblocks] energy partials
     shell::DevArray<shell::ForceDesc> fdesc;     // descriptor for the caller-order entry point
     shell::DevArray<shell::WorkItem> tile_items; // (0, tile) for every tile
+    shell::DevArray<uint32_t> arrived;           // arrival counters of its energy sum
 };
 
 namespace shell {
@@ -555,17 +566,20 @@ void launch_clamp_bias(shell_stencils_s& st, const int32_t* bc, hipStream_t s);
 // one launch per model over a list of (mesh, tile) items; lds_T = the largest tile among the meshes
 // start/stop: events that receive the kernel's own begin and end times (null: none)
 void launch_force_items(int model, int precision, const ForceDesc* descs, const WorkItem* items, long nitems,
-                        int lds_T, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// writes the descriptor *dst = d and the tile items (0, t), t < ntiles, from a kernel
-void launch_write_force_desc(const ForceDesc& d, ForceDesc* dst, WorkItem* items, int64_t ntiles, hipStream_t s);
-// energy = add + sum of the n partials (+ the m partials of `extra`, when given)
-void launch_energy_finalize(const double* epart, int64_t n, double add, double* energy, hipStream_t s,
-                            const double* extra = nullptr, int64_t m = 0);
+                        int lds_T, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
+                        const ForceCaller& caller = {});
+// writes the descriptor *dst = d, the tile items (0, t), t < ntiles, and their arrival counters from a kernel
+void launch_write_force_desc(const ForceDesc& d, ForceDesc* dst, WorkItem* items, uint32_t* arrived, int64_t ntiles,
+                             hipStream_t s);
+// *energy = 0 from a kernel (a mesh without vertices)
+void launch_zero_energy(double* energy, hipStream_t s);
 // membrane.hip: rest data of the membrane (SHELL_FLAG_MEMBRANE); its force added into f (internal order,
 // double or float per the stencils' precision) from the float64 positions pos
 void launch_membrane_rest(shell_stencils_s& st, hipStream_t s);
-// epart: where the tiles' energy partials go (the stencils' own array when null)
-void launch_membrane_forces(shell_stencils_s& st, const double* pos, void* f, hipStream_t s, double* epart = nullptr);
+// epart: where the tiles' energy partials go (the stencils' own array when null); caller: its force is the sum of
+// f and the membrane's, its energy that of the bending partials `bend` too
+void launch_membrane_forces(shell_stencils_s& st, const double* pos, void* f, hipStream_t s, double* epart = nullptr,
+                            const ForceCaller& caller = {}, const double* bend = nullptr);
 // the implicit step with the membrane: set-up once per simulation, then one step (float64)
 void membrane_sim_init(shell_sim_s& sim, hipStream_t s);
 shell_status_t membrane_step(shell_sim_s& sim, const shell_step_params_t& p, shell_step_stats_t& out,

@@ -72,7 +72,8 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
                                                                const double* __restrict__ trest,
                                                                const int64_t* __restrict__ boff, long nv, int T,
                                                                double c, double nu, double scale,
-                                                               R* __restrict__ f, double* __restrict__ epart) {
+                                                               R* __restrict__ f, double* __restrict__ epart,
+                                                               ForceCaller caller, const double* __restrict__ bend) {
     extern __shared__ unsigned char smem_raw[];
     const long blk = blockIdx.x;
     const long base = blk * long(T);
@@ -81,14 +82,19 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
     acc.clear(3 * nown);
     const double inv_scale = acc.kUnit / scale;  // counts per force unit, a power of two: exact
     __syncthreads();
+    const int32_t* cperm = caller.x ? caller.perm : nullptr;
+    if (caller.x) pos = caller.x;
     double en[1] = {0.0};
     const long e0 = boff[2 * blk], e1 = boff[2 * blk + 1];
     for (long e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
         const long v[3] = {tid[4 * e], tid[4 * e + 1], tid[4 * e + 2]};
         double d1[3], d2[3];
-        for (int i = 0; i < 3; ++i) {
-            d1[i] = pos[3 * v[1] + i] - pos[3 * v[0] + i];
-            d2[i] = pos[3 * v[2] + i] - pos[3 * v[0] + i];
+        {
+            const long r0 = cperm ? cperm[v[0]] : v[0], r1 = cperm ? cperm[v[1]] : v[1], r2 = cperm ? cperm[v[2]] : v[2];
+            for (int i = 0; i < 3; ++i) {
+                d1[i] = pos[3 * r1 + i] - pos[3 * r0 + i];
+                d2[i] = pos[3 * r2 + i] - pos[3 * r0 + i];
+            }
         }
         const double G[2][2] = {{trest[6 * e], trest[6 * e + 1]}, {trest[6 * e + 2], trest[6 * e + 3]}};
         const double A = trest[6 * e + 4];
@@ -113,10 +119,22 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
     __syncthreads();
     R* out = f + 3 * base;
     const double sc = scale;
-    for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[i] = R(double(out[i]) + acc.get(i) * sc);
+    if (caller.f) {
+        R* cf = static_cast<R*>(caller.f);
+        for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x)
+            cf[3L * caller.perm[base + i / 3] + i % 3] = R(double(out[i]) + acc.get(i) * sc);
+    } else {
+        for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[i] = R(double(out[i]) + acc.get(i) * sc);
+    }
     __shared__ double sh[kMembThreads / 64];
+    if (caller.energy)  // with the bending energy of the tile, complete since the kernel before
+        if (threadIdx.x == 0) en[0] += bend[blk];
     block_sum<1>(en, sh);
-    if (threadIdx.x == 0) epart[blk] = en[0];
+    if (!caller.energy) {
+        if (threadIdx.x == 0) epart[blk] = en[0];
+    } else if (last_block_sum(en[0], blk, gridDim.x, epart, caller.arrived, sh)) {
+        if (threadIdx.x == 0) *caller.energy = en[0] + caller.add;
+    }
 }
 
 // ---------------------------------------------------------------- implicit step with the membrane
@@ -929,19 +947,21 @@ void launch_membrane_rest(shell_stencils_s& st, hipStream_t s) {
     SHELL_HIP(hipStreamSynchronize(s));  // the temporaries are released on return
 }
 
-void launch_membrane_forces(shell_stencils_s& st, const double* pos, void* f, hipStream_t s, double* epart) {
+void launch_membrane_forces(shell_stencils_s& st, const double* pos, void* f, hipStream_t s, double* epart,
+                            const ForceCaller& caller, const double* bend) {
     if (st.nv == 0 || st.nblocks == 0) return;
     double* ep = epart ? epart : st.mepart.p;
     const double c = st.young * st.thickness / (1.0 - st.poisson * st.poisson);
     const unsigned grid = unsigned(st.nblocks);
+    auto launch = [&](auto real, size_t lds) {
+        using R = decltype(real);
+        membrane_tiles<R><<<grid, kMembThreads, lds, s>>>(pos, st.mtid.p, st.mtrest.p, st.mboff.p, st.nv, st.T, c,
+                                                          st.poisson, st.mscale, static_cast<R*>(f), ep, caller, bend);
+    };
     if (st.precision == SHELL_PREC_MIXED)
-        membrane_tiles<float><<<grid, kMembThreads, TileAccT<1>::bytes(st.T), s>>>(pos, st.mtid.p, st.mtrest.p, st.mboff.p,
-                                                              st.nv, st.T, c, st.poisson, st.mscale, static_cast<float*>(f),
-                                                              ep);
+        launch(0.0f, TileAccT<1>::bytes(st.T));
     else
-        membrane_tiles<double><<<grid, kMembThreads, TileAccT<2>::bytes(st.T), s>>>(pos, st.mtid.p, st.mtrest.p, st.mboff.p,
-                                                               st.nv, st.T, c, st.poisson, st.mscale, static_cast<double*>(f),
-                                                               ep);
+        launch(0.0, TileAccT<2>::bytes(st.T));
     SHELL_HIP(hipGetLastError());
 }
 

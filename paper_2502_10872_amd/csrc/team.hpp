@@ -47,22 +47,10 @@ __device__ __forceinline__ double* team_set(double* slots, int members, int set,
     return slots + (size_t(set) * 2 + size_t(par & 1)) * kTeamQ * size_t(members);
 }
 
-template <typename T>
-__device__ __forceinline__ void agent_store(T* p, T v) {
-    __hip_atomic_store(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ T agent_load(const T* p) {
-    return __hip_atomic_load(G(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ void team_publish(double* slot, double v) {
     const unsigned long long u = __builtin_isnan(v) ? kPlainNan : (unsigned long long)__double_as_longlong(v);
     agent_store(reinterpret_cast<unsigned long long*>(slot), u);
 }
-
-// every store of this wave has reached memory
-__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // The sum of v over the wave, in lane 63 (the other lanes hold partial sums): rows of 16 by shifts, then the
 // rows' ends broadcast to the rows after them.  Register moves between lanes instead of LDS permutes: six of

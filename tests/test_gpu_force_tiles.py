@@ -48,3 +48,44 @@ def test_default_tiles_give_the_forces_of_whole_ordering_tiles(model, n, block, 
     for (f, e), (fw, ew) in zip(got, want):
         assert np.array_equal(f, fw)
         assert abs(e - ew) <= 1e-12 * abs(ew)
+
+
+# one tile; a whole group of 16 arrivals; one work-group alone in its group; two groups and a remainder
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("model,nv_tiles,flags", [
+    ("EP", 1, 0), ("SS", 16, 0), ("ES", 17, S.SHELL_FLAG_MEMBRANE), ("FP", 39, S.SHELL_FLAG_MEMBRANE)])
+def test_forces_written_over_the_positions_and_energy_of_all_tiles(model, nv_tiles, flags, precision):
+    """Forces into the memory of the positions (gathered first) equal forces into memory of their own (read where
+    they lie), call after call, and the energy equals a central difference's: f = -dE/dx along f itself."""
+    mesh = I.plate_mesh(int(np.sqrt(64 * nv_tiles)), 1.0, 0.2, 7, model)
+    if model.endswith("S"):
+        mesh = I.workload_sphere_cap(int(np.sqrt(64 * nv_tiles)), model)
+    x = mesh.X + 1e-2 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
+    real = torch.float32 if precision == S.SHELL_PREC_MIXED else torch.float64
+    with S.Problem(mesh, I.MATERIAL, model=model, precision=precision, block_vertices=64, flags=flags,
+                   sim=False) as pb:
+        assert pb.info["nblocks"] == -(-mesh.nv // 64)
+        xd = torch.as_tensor(x, device="cuda")
+        f = torch.empty(mesh.nv, 3, device="cuda", dtype=real)
+        e = torch.zeros(3, device="cuda", dtype=torch.float64)
+        for call in (S.shell_eval_forces, S.shell_eval_forces_noalloc):
+            for _ in range(3):
+                call(pb.st, xd, f, e)
+                over = xd.clone()
+                call(pb.st, over, over, e[1:])
+                torch.cuda.synchronize()
+                inside = over.flatten().view(real)[:3 * mesh.nv].view(mesh.nv, 3)
+                assert torch.equal(inside, f)
+                assert float(e[0]) == float(e[1])
+        g = f.double().clone()
+        h = 1e-4 * mesh.spacing / float(g.abs().max())
+        ends = []
+        for sign in (1.0, -1.0):
+            S.shell_eval_forces(pb.st, xd + sign * h * g, f, e)
+            torch.cuda.synchronize()
+            ends.append(float(e[0]))
+    # central difference: third-order terms are 1e-8 of the first; the energies' own rounding (float32: 1e-7 of a
+    # total some 1e2 to 1e4 times the difference) dominates
+    want = -2 * h * float((g * g).sum())
+    noise = (1e-6 if precision == S.SHELL_PREC_MIXED else 1e-13) * abs(ends[0])
+    assert abs((ends[0] - ends[1]) - want) <= 1e-3 * abs(want) + noise
