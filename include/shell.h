@@ -75,9 +75,8 @@ typedef struct {
 
 typedef struct {
     int32_t precision;       /* shell_precision_t */
-    int32_t block_vertices;  /* vertices per force work-group tile, 64..4096; 0 selects the default: vertices
-                                ordered in tiles of 2048, and 2048 or fewer per work-group (at least 128) so
-                                that a mesh fills the chip */
+    int32_t block_vertices;  /* vertices per force work-group tile, 64..4096; 0 selects the default: 64 to 2048
+                                by the mesh's size, so that its tiles fill the chip */
     int32_t reorder;         /* internal vertex order: 1 (default) recursive coordinate bisection into compact
                                 tiles of block_vertices, 2 Morton order, 0 the caller's order */
     int32_t flags;           /* 0, or SHELL_FLAG_DIRECT_PRODUCT, SHELL_FLAG_WORLD_FRAME, SHELL_FLAG_MEMBRANE */

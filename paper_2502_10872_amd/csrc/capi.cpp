@@ -68,15 +68,23 @@ void check_params(const shell_step_params_t& p) {
             SHELL_CHECK(p.replay_counts[q] >= 0, SHELL_E_INVALID_ARG, "negative replay count");
 }
 
-// Vertices per force work-group when the caller leaves the choice: the vertices are ordered in tiles of `order`
-// (2048); a work-group takes a power of two of them, at least 128, that makes at most 512 work-groups (two per
-// CU), so that meshes of all sizes fill the chip: at 2048 a mesh of 65536 vertices kept 32 of 256 CUs busy.
-// More, smaller work-groups only repeat more boundary stencils.  shell_eval_forces at 65536 vertices, 2048, 512,
-// 256, 128 and 64 vertices: ES with membrane FP64 60.4, 28.0, 22.8, 23.4, 30.1 us, SS mixed 34.9, 18.4, 16.2,
-// 15.7, 19.8; at 262144, 2048, 512 and 128: SS FP64 55.2, 43.2, 52.0; at 524176, 2048 and 512: 72.5, 74.7.
-int force_tile_vertices(int64_t nv, int order) {
-    int t = 128;
-    while (t < order && nv > int64_t(512) * t) t *= 2;
+// Tiles of the vertex order when the caller leaves the choice.  Up to 65536 vertices they are larger than the force
+// tiles, which then are runs of the order inside them (SS FP64 17.7 us against 14.4 with an order in
+// tiles of 128 at 65536 vertices, 10.0 against 9.5 at 16384); above the order has the force tiles' own size: at 142129
+// vertices SS FP64 28.3 us against 32.4, ES with membrane 35.2 against 38.1, at 262144 34.6 and 40.6 against 40.4
+// and 42.9.
+constexpr int kOrderTile = 2048;
+constexpr int64_t kOrderRuns = 65536;
+
+// Vertices per force work-group when the caller leaves the choice: a power of two from 64 to 2048 that makes at
+// most 512 work-groups (two per CU), so that meshes of all sizes fill the chip: at 2048 a mesh of 65536 vertices
+// kept 32 of 256 CUs busy.  More, smaller work-groups only repeat more boundary stencils.  shell_eval_forces at
+// 142129 vertices, 2048, 1024, 512, 256 and 128 vertices: ES with membrane FP64 73.9, 44.6, 35.6, 36.2, 38.4 us, SS
+// mixed 42.7, 25.6, 21.6, 24.5, 25.2; at 524176, 2048, 1024, 512: SS FP64 72.6, 60.3, 70.4; at 16384, 2048, 128,
+// 64: 40.9, 9.5, 8.8.
+int force_tile_vertices(int64_t nv) {
+    int t = 64;
+    while (t < kOrderTile && nv > int64_t(512) * t) t *= 2;
     return t;
 }
 
@@ -129,7 +137,8 @@ shell_status_t shell_build_stencils(const double* X, int64_t nv, const int32_t* 
         int precision = cfg ? cfg->precision : SHELL_PREC_FP64;
         SHELL_CHECK(precision == SHELL_PREC_FP64 || precision == SHELL_PREC_MIXED, SHELL_E_INVALID_ARG,
                     "unknown precision");
-        int T = (cfg && cfg->block_vertices > 0) ? cfg->block_vertices : 2048;
+        const bool given = cfg && cfg->block_vertices > 0;
+        const int T = given ? cfg->block_vertices : force_tile_vertices(nv);
         SHELL_CHECK(T >= 64 && T <= 4096, SHELL_E_INVALID_ARG, "block_vertices must be in [64, 4096]");
         int reorder = cfg ? cfg->reorder : 1;
         SHELL_CHECK(reorder >= 0 && reorder <= 2, SHELL_E_INVALID_ARG, "unknown vertex order");
@@ -147,7 +156,7 @@ shell_status_t shell_build_stencils(const double* X, int64_t nv, const int32_t* 
         st->precision = precision;
         st->nv = nv;
         st->nt = nt;
-        st->T = (cfg && cfg->block_vertices > 0) ? T : force_tile_vertices(nv, T);
+        st->T = T;
         st->cfg_flags = cfg_flags;
         st->young = mat->young;
         st->poisson = mat->poisson;
@@ -176,7 +185,7 @@ shell_status_t shell_build_stencils(const double* X, int64_t nv, const int32_t* 
 
         const int k = st->k, r = st->r;
         st->ns = topo.ns;
-        st->perm = vertex_order(X, nv, reorder, T);
+        st->perm = vertex_order(X, nv, reorder, given || nv > kOrderRuns ? T : kOrderTile);
         st->reordered = reorder != 0;
         st->iperm.assign(size_t(nv), 0);
         for (int64_t i = 0; i < nv; ++i) st->iperm[size_t(st->perm[size_t(i)])] = int32_t(i);
@@ -334,7 +343,8 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 
 // Forces from and into the caller's order.  The kernels read positions and write forces through the permutation
 // themselves: gather, scatter and energy kernels around them made 15 us of launches at any small size (now 7-8 us)
-// and passes over memory at the large ones (1M vertices, SS mixed 89.6 -> 79.8 us, SS FP64 129.5 -> 111.8; 142K, ES with membrane FP64 39.6 -> 36.5).
+// and passes over memory at the large ones (1M vertices, SS mixed 89.6 -> 79.8 us, SS FP64 129.5 -> 111.8; 142K,
+// ES with membrane FP64 39.6 -> 36.5).
 // Where f overlaps x the positions are gathered first, since a tile's forces go out while others still read.
 void launch_caller_forces(shell_stencils_s& st, const double* x, void* f, double* energy, double* xin, void* fout,
                           double* epart, const ForceDesc* desc, const WorkItem* items, uint32_t* arrived,

@@ -547,18 +547,22 @@ int force_threads(Kernel kernel) {
     return std::min(kMaxForceThreads, 256 * std::max(1, waves / 2));
 }
 
+// A tile of 64 vertices has about 200 stencils: more than 8 threads per vertex would only start and end.
+constexpr int kForceThreadsPerVertex = 8;
+
 template <int MODEL>
 void launch_model(int precision, const ForceDesc* descs, const WorkItem* items, long nitems, int lds_T,
                   hipStream_t s, hipEvent_t start, hipEvent_t stop, const ForceCaller& caller) {
     static const int threads_d = force_threads(force_tiles<MODEL, double>);
     static const int threads_f = force_threads(force_tiles<MODEL, float>);
     const dim3 grid(unsigned(xcd_grid(nitems)));
+    const int most = kForceThreadsPerVertex * lds_T;
     // start/stop (may be null) receive the dispatch's own begin and end times
     if (precision == SHELL_PREC_FP64)
-        hipExtLaunchKernelGGL(force_tiles<MODEL, double>, grid, dim3(threads_d), uint32_t(TileAccT<2>::bytes(lds_T)),
+        hipExtLaunchKernelGGL(force_tiles<MODEL, double>, grid, dim3(std::min(threads_d, most)), uint32_t(TileAccT<2>::bytes(lds_T)),
                               s, start, stop, 0, descs, items, nitems, caller);
     else
-        hipExtLaunchKernelGGL(force_tiles<MODEL, float>, grid, dim3(threads_f), uint32_t(TileAccT<1>::bytes(lds_T)),
+        hipExtLaunchKernelGGL(force_tiles<MODEL, float>, grid, dim3(std::min(threads_f, most)), uint32_t(TileAccT<1>::bytes(lds_T)),
                               s, start, stop, 0, descs, items, nitems, caller);
     SHELL_HIP(hipGetLastError());
 }

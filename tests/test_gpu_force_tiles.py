@@ -1,7 +1,8 @@
-"""The default size of a force work-group's vertex tile against tiles of 2048 vertices set by the caller.
+"""The default size of a force work-group's vertex tile against tiles of 2048 vertices set by the caller, and forces
+from and into the caller's own arrays.
 
-The default orders the vertices in tiles of 2048 too, so the two share the vertex order; the fixed-point
-accumulation adds the same integers per vertex whatever the tile, so the forces agree bit for bit.  The energy
+A stencil's force does not depend on its vertices' internal numbers, and the fixed-point accumulation adds the
+same integers per vertex whatever the tile, so the forces agree bit for bit.  The energy
 is summed per tile in float64: with E the sum of some 1e5 terms of one sign the two groupings differ by less
 than 1e-12 of it."""
 
@@ -31,14 +32,14 @@ def eval_forces(mesh, x, model, precision, block, flags):
         return out, pb.info
 
 
-# one tile; the last vertex alone in its tile; either side of the first change of size (512 tiles of 128);
-# tiles of 512; the largest mesh below whole ordering tiles
+# one tile; ragged last tiles; either side of each change of size (512 tiles of 64, 128, ...), the second of which
+# is the change of the vertex order too
 @pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
 @pytest.mark.parametrize("model,n,block,flags", [
-    ("EP", 5, 128, 0), ("FP", 23, 128, 0), ("SS", 43, 128, S.SHELL_FLAG_MEMBRANE), ("ES", 256, 128, 0),
-    ("FS", 257, 256, S.SHELL_FLAG_MEMBRANE), ("SP", 512, 512, 0), ("ES", 700, 1024, S.SHELL_FLAG_MEMBRANE),
-    ("SS", 725, 2048, 0)])
-def test_default_tiles_give_the_forces_of_whole_ordering_tiles(model, n, block, flags, precision):
+    ("EP", 5, 64, 0), ("FP", 23, 64, 0), ("SS", 43, 64, S.SHELL_FLAG_MEMBRANE), ("SP", 181, 64, 0),
+    ("EP", 182, 128, 0), ("ES", 256, 128, 0), ("FS", 257, 256, S.SHELL_FLAG_MEMBRANE), ("SP", 512, 512, 0),
+    ("ES", 700, 1024, S.SHELL_FLAG_MEMBRANE), ("SS", 725, 2048, 0)])
+def test_default_tiles_give_the_forces_of_tiles_of_2048(model, n, block, flags, precision):
     mesh = I.plate_mesh(n, 1.0, 0.2, 7, model) if model.endswith("P") else I.workload_sphere_cap(n, model)
     x = mesh.X + 1e-3 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
     got, info = eval_forces(mesh, x, model, precision, 0, flags)
