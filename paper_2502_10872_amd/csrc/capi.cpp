@@ -567,19 +567,24 @@ shell_status_t shell_hessian_apply(shell_hessian_t h, const double* mass, double
         const shell_stencils_s& st = *h->st;
         const long nv = st.nv;
         if (!nv) return SHELL_OK;
-        if (!h->pin.p) {  // caller-order staging, made on first use
+        if (!h->pin.p) {  // staging of p and mass, made on first use
             h->pin.alloc(size_t(3 * nv));
-            h->qout.alloc(size_t(4 * nv));
+            h->min.alloc(size_t(nv));
         }
-        double* min = nullptr;
-        if (mass) {
-            min = h->qout.p + 3 * nv;
-            gather1<<<(nv + 255) / 256, 256, 0, s>>>(mass, st.perm_d.p, min, nv);
-            SHELL_HIP(hipGetLastError());
+        // q over p or the masses, or a product that isn't staged: the inputs are gathered first
+        const size_t bytes = size_t(nv) * sizeof(double);
+        const bool through = h->gptr.p && !overlap(q, 3 * bytes, p, 3 * bytes) &&
+                             !(mass && overlap(q, 3 * bytes, mass, bytes));
+        if (!through) {
+            if (mass) {
+                gather1<<<(nv + 255) / 256, 256, 0, s>>>(mass, st.perm_d.p, h->min.p, nv);
+                SHELL_HIP(hipGetLastError());
+                mass = h->min.p;
+            }
+            launch_gather_rows(p, st.perm_d.p, h->pin.p, nv, s);
+            p = h->pin.p;
         }
-        launch_gather_rows(p, st.perm_d.p, h->pin.p, nv, s);
-        launch_apply(*h, min, dt2, h->pin.p, h->qout.p, s);
-        launch_scatter_rows(h->qout.p, st.perm_d.p, q, nv, false, s);
+        launch_apply(*h, mass, dt2, p, q, s, st.perm_d.p, through);
         return SHELL_OK;
     });
 }
@@ -932,7 +937,7 @@ shell_status_t shell_sim_device_bytes(shell_sim_t sim, int64_t* stencil_bytes, i
                          st.mtid.bytes(), st.mtrest.bytes(), st.mboff.bytes(), st.mepart.bytes()})
             a += int64_t(v);
         for (size_t v : {h.scol.bytes(), h.width.bytes(), h.sptr.bytes(), h.rowlen.bytes(), h.val.bytes(),
-                         h.valf.bytes(), h.kdiag.bytes(), h.pin.bytes(), h.qout.bytes(), h.gptr.bytes(),
+                         h.valf.bytes(), h.kdiag.bytes(), h.pin.bytes(), h.min.bytes(), h.gptr.bytes(),
                          h.gcols.bytes(), h.lcol.bytes(), h.tptr.bytes(), h.twid.bytes(), h.tval.bytes(),
                          h.tvalf.bytes()})
             b += int64_t(v);

@@ -587,17 +587,6 @@ __global__ void gather_rows(const double* __restrict__ src, const int32_t* __res
     dst[3 * i + 2] = src[3 * u + 2];
 }
 
-template <typename T>
-__global__ void scatter_rows(const T* __restrict__ src, const int32_t* __restrict__ perm, T* __restrict__ dst,
-                             long nv) {
-    long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
-    if (i >= nv) return;
-    long u = perm[i];
-    dst[3 * u] = src[3 * i];
-    dst[3 * u + 1] = src[3 * i + 1];
-    dst[3 * u + 2] = src[3 * i + 2];
-}
-
 }  // namespace
 
 void launch_force_items(int model, int precision, const ForceDesc* descs, const WorkItem* items, long nitems,
@@ -629,17 +618,6 @@ void launch_zero_energy(double* energy, hipStream_t s) {
 void launch_gather_rows(const double* src, const int32_t* perm, double* dst, int64_t nv, hipStream_t s) {
     if (!nv) return;
     gather_rows<<<(nv + 255) / 256, 256, 0, s>>>(src, perm, dst, nv);
-    SHELL_HIP(hipGetLastError());
-}
-
-void launch_scatter_rows(const void* src, const int32_t* perm, void* dst, int64_t nv, bool f32, hipStream_t s) {
-    if (!nv) return;
-    if (f32)
-        scatter_rows<float><<<(nv + 255) / 256, 256, 0, s>>>(static_cast<const float*>(src), perm,
-                                                             static_cast<float*>(dst), nv);
-    else
-        scatter_rows<double><<<(nv + 255) / 256, 256, 0, s>>>(static_cast<const double*>(src), perm,
-                                                              static_cast<double*>(dst), nv);
     SHELL_HIP(hipGetLastError());
 }
 

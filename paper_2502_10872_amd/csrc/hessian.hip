@@ -144,29 +144,47 @@ __global__ void team_columns(const int32_t* __restrict__ scol, const int64_t* __
     while (o < 2 * twid[s]) put(self);
 }
 
-// q = diag(mass) p + dt2 K_s p over 3 columns (caller order handled by the host wrapper)
+// q = diag(mass) p + dt2 K_s p over 3 columns.  With `perm` q is in the caller's order, and with THROUGH p and mass
+// are too: the matrix stream bounds the kernel (262144 rows of 19 entries: 50 of 65 MB, 10.4 us at the rate of a
+// copy), and gather and scatter kernels around it took as long again (24.9 us; now 13.4).
+template <bool THROUGH>
 __global__ void apply_sell(const int32_t* __restrict__ scol, const double* __restrict__ val,
                            const int64_t* __restrict__ sptr, const int32_t* __restrict__ width,
                            const int32_t* __restrict__ gptr, const int32_t* __restrict__ gcols,
-                           const uint16_t* __restrict__ lcol, long nv, const double* __restrict__ mass, double dt2,
-                           const double* __restrict__ p, double* __restrict__ q) {
+                           const uint16_t* __restrict__ lcol, long nv, const int32_t* __restrict__ perm,
+                           const double* __restrict__ mass, double dt2, const double* __restrict__ p,
+                           double* __restrict__ q) {
     long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
     extern __shared__ unsigned char smem_raw[];
     double* ps = reinterpret_cast<double*>(smem_raw);
-    if (gptr) {
-        stage_group_columns<double>(gptr, gcols, blockIdx.x, p, ps);
+    const long to = perm && i < nv ? perm[i] : i;  // where row i goes
+    const long from = THROUGH ? to : i;
+    double m = 0.0, px = 0.0, py = 0.0, pz = 0.0;
+    if (i < nv) {
+        if (mass) m = mass[from];
+        px = p[3 * from];
+        py = p[3 * from + 1];
+        pz = p[3 * from + 2];
+    }
+    if (THROUGH || gptr) {
+        const int a = gptr[blockIdx.x], n = gptr[blockIdx.x + 1] - a;
+        for (int k = threadIdx.x; k < n; k += blockDim.x) {
+            const long c = THROUGH ? perm[gcols[a + k]] : gcols[a + k];
+            ps[3 * k] = p[3 * c];
+            ps[3 * k + 1] = p[3 * c + 1];
+            ps[3 * k + 2] = p[3 * c + 2];
+        }
         __syncthreads();
     }
     if (i >= nv) return;
     double ax, ay, az;
-    if (gptr)
+    if (THROUGH || gptr)
         sell_row_product_staged<double, double>(lcol, val, sptr, width, i, ps, ax, ay, az);
     else
         sell_row_product<double, double>(scol, val, sptr, width, i, p, ax, ay, az);
-    double m = mass ? mass[i] : 0.0;
-    q[3 * i] = fma(m, p[3 * i], dt2 * ax);
-    q[3 * i + 1] = fma(m, p[3 * i + 1], dt2 * ay);
-    q[3 * i + 2] = fma(m, p[3 * i + 2], dt2 * az);
+    q[3 * to] = fma(m, px, dt2 * ax);
+    q[3 * to + 1] = fma(m, py, dt2 * ay);
+    q[3 * to + 2] = fma(m, pz, dt2 * az);
 }
 
 }  // namespace
@@ -345,13 +363,14 @@ const TeamPart* team_part(shell_hessian_s& h, int64_t rows, hipStream_t s) {
 }
 
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,
-                  hipStream_t s) {
+                  hipStream_t s, const int32_t* perm, bool through) {
     const long nv = h.pat.nv;
     if (!nv) return;
-    size_t lds = h.gptr.p ? size_t(h.pat.max_gcols) * 3 * sizeof(double) : 0;
-    apply_sell<<<(nv + kRowGroup - 1) / kRowGroup, kRowGroup, lds, s>>>(h.scol.p, h.val.p, h.sptr.p, h.width.p,
-                                                                      h.gptr.p, h.gcols.p, h.lcol.p, nv, mass, dt2,
-                                                                      p, q);
+    const size_t lds = h.gptr.p ? size_t(h.pat.max_gcols) * 3 * sizeof(double) : 0;
+    const unsigned grid = unsigned((nv + kRowGroup - 1) / kRowGroup);
+    auto* kernel = through ? apply_sell<true> : apply_sell<false>;
+    kernel<<<grid, kRowGroup, lds, s>>>(h.scol.p, h.val.p, h.sptr.p, h.width.p, h.gptr.p, h.gcols.p, h.lcol.p, nv, perm,
+                                        mass, dt2, p, q);
     SHELL_HIP(hipGetLastError());
 }
 

@@ -369,7 +369,7 @@ struct shell_hessian_s {
     shell::DevArray<double> val;         // [nslots]
     shell::DevArray<float> valf;         // [nslots] mixed copy
     shell::DevArray<double> kdiag;       // [nv]
-    shell::DevArray<double> pin, qout;   // caller-order scratch for hessian_apply
+    shell::DevArray<double> pin, min;    // p and the masses in internal order, for hessian_apply
 };
 
 
@@ -596,11 +596,11 @@ void membrane_time_kernels(shell_sim_s& sim, double dt, int reps, shell_kernel_t
 shell_status_t membrane_batch_step(shell_batch_s& b, const shell_step_params_t* p, int nparams,
                                    shell_step_stats_t* stats, hipStream_t s);
 void launch_gather_rows(const double* src, const int32_t* perm, double* dst, int64_t nv, hipStream_t s);
-void launch_scatter_rows(const void* src, const int32_t* perm, void* dst, int64_t nv, bool f32, hipStream_t s);
 // hessian.hip
 void launch_assemble(shell_hessian_s& h, hipStream_t s);
+// perm: q in the caller's order; through (staged patterns only): p and mass in it too
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,
-                  hipStream_t s);
+                  hipStream_t s, const int32_t* perm = nullptr, bool through = false);
 // rows per member of a mesh on its own; one member up to `alone` rows, then one per compute unit, of `least` rows
 int64_t team_rows(int64_t nv);
 int64_t team_rows_spread(int64_t nv, int64_t alone, int64_t least);

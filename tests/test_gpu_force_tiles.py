@@ -90,3 +90,33 @@ def test_forces_written_over_the_positions_and_energy_of_all_tiles(model, nv_til
     want = -2 * h * float((g * g).sum())
     noise = (1e-6 if precision == S.SHELL_PREC_MIXED else 1e-13) * abs(ends[0])
     assert abs((ends[0] - ends[1]) - want) <= 1e-3 * abs(want) + noise
+
+
+# one row group and a ragged one; whole groups; the product that isn't staged
+@pytest.mark.parametrize("model,n,flags", [("EP", 5, 0), ("SS", 32, 0), ("FP", 45, 0), ("ES", 300, 0),
+                                           ("SS", 45, S.SHELL_FLAG_DIRECT_PRODUCT)])
+def test_operator_product_over_its_inputs(model, n, flags):
+    """q = diag(m) p + dt^2 K p read where p and m lie equals the product over p's and over m's own memory bit
+    for bit, and the product without masses plus m p to float64 rounding (1e-13 of the largest value)."""
+    mesh = I.plate_mesh(n, 1.0, 0.2, 7, model) if model.endswith("P") else I.workload_sphere_cap(n, model)
+    g = I.rng(9)
+    p, mass = g.standard_normal((mesh.nv, 3)), g.uniform(0.5, 1.5, mesh.nv)
+    with S.Problem(mesh, I.MATERIAL, model=model, flags=flags) as pb:
+        pd, md = torch.as_tensor(p, device="cuda"), torch.as_tensor(mass, device="cuda")
+        for m in (md, None):
+            q = torch.full_like(pd, float("nan"))
+            S.shell_hessian_apply(pb.h, m, 0.25, pd, q)
+            over = pd.clone()
+            S.shell_hessian_apply(pb.h, m, 0.25, over, over)
+            one = torch.full_like(pd, float("nan"))
+            S.shell_hessian_apply(pb.h, None, 0.25, pd, one)
+            torch.cuda.synchronize()
+            assert torch.equal(over, q)
+            want = one if m is None else one + m[:, None] * pd
+            bound = 1e-13 * float(want.abs().max())
+            assert float((q - want).abs().max()) <= bound
+        both = torch.cat([md, torch.zeros(2 * mesh.nv, device="cuda", dtype=torch.float64)])
+        S.shell_hessian_apply(pb.h, both[:mesh.nv], 0.25, pd, both.view(mesh.nv, 3))
+        S.shell_hessian_apply(pb.h, md, 0.25, pd, q)
+        torch.cuda.synchronize()
+        assert torch.equal(both.view(mesh.nv, 3), q)
