@@ -28,11 +28,16 @@ namespace {
 // where the previous launch of the same solve stopped.
 enum : int { kTeamFresh = 0, kTeamRefine = 1, kTeamResume = 2 };
 
-// A member runs 512 threads (two waves per SIMD, 256 registers each).  With up to 1024 rows it holds the first
-// kTeamPairs pairs of each row's entries in registers for the whole solve (nine pairs: the eighteen neighbours
-// of a regular triangle-model row), so that an iteration reads no matrix at all; with more it streams it in
-// batches of kTeamBatch pairs.
+// A member runs 512 threads (two waves per SIMD, 256 registers each).  It holds the first kTeamResident pairs of each
+// row's entries in registers for the whole solve: with up to 1024 rows, in mixed precision up to 1536, nine pairs
+// (the eighteen neighbours of a regular triangle-model row), so that an iteration reads no matrix at all, with
+// up to 1536 in float64 a third of them; the others it streams in batches of kTeamBatch pairs.  The three rows per
+// thread at 393129 vertices: 24.4 -> 23.1 us per iteration FP64 and 18.5 -> 16.2 mixed against streaming all.  With
+// four rows and more, holding some pairs shortens the batches and not their number: 26.9 -> 27.9 us FP64 (two
+// pairs), 20.6 -> 20.0 mixed (six) at 524176, 27.0 -> 26.1 mixed (three) at 784996, and 1M spills.
 constexpr int kTeamPairs = 9;
+template <typename MR, int RPL>
+constexpr int kTeamResident = RPL <= 2 ? kTeamPairs : RPL == 3 ? (sizeof(MR) == 8 ? 3 : kTeamPairs) : 0;
 template <typename MR>
 constexpr int kTeamBatch = sizeof(MR) == 8 ? 3 : 9;
 
@@ -49,7 +54,9 @@ __global__ __launch_bounds__(kTeamThreads) void k_team_pcg(const SolveDesc* __re
                                                 uint64_t wait_ticks) {
     typedef typename Pair<MR>::type MR2;
     constexpr bool mixed = sizeof(VR) == 4;
-    constexpr int T = kTeamThreads, NW = T / 64, B = kTeamBatch<MR>, RES = RPL <= 2 ? kTeamPairs : 0, REM = RES > 0 ? 2 : 3;
+    constexpr int T = kTeamThreads, NW = T / 64, B = kTeamBatch<MR>, RES = kTeamResident<MR, RPL>,
+                  REM = RES == kTeamPairs ? 2 : 3;
+    static_assert(RES % 3 == 0, "the held pairs are used in threes");
     extern __shared__ unsigned char smem_raw[];
     VR* ps = reinterpret_cast<VR*>(smem_raw);
     __shared__ double shA[3 * NW], outA[3 * NW], shB[6 * NW], outB[6 * NW];
@@ -355,7 +362,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team_pcg(const SolveDesc* __re
             }
             const gbl<const MR2>* gv = G(static_cast<const MR2*>(d.tval)) + tp0 + off[s];
             const gbl<const uint32_t>* gc = G(d.tcol) + tp0 + off[s];
-            if constexpr (RES == 0)
+            if constexpr (RES < kTeamPairs)
                 for (; k + B <= w[s]; k += B) {
                     MR2 v[B];
                     uint32_t cc[B];
