@@ -547,10 +547,8 @@ struct shell_batch_s {
     shell::SolveDesc* sdesc_host = nullptr;  // pinned staging
     shell::ForceDesc* fdesc_host = nullptr;
     shell::WorkItem* items_host = nullptr;
-    int32_t* mlist_host = nullptr;
     size_t items_cap = 0;
     shell::DevArray<shell::WorkItem> items;   // [rows | tiles of each model]
-    shell::DevArray<int32_t> mlist;
     bool membrane = false;  // simulations with the membrane: the members' steps interleave on their own streams
     uint64_t team_wait = ~uint64_t(0);  // ticks a team's wait may take (tests shorten it)
 };

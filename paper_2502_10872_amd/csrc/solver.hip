@@ -291,11 +291,13 @@ struct ItemBuilder {
 };
 
 // Copies the item lists through pinned staging to the batch's device item buffer.  The stream is
-// drained first: earlier copies from the staging and earlier kernels reading the device buffer must
-// have finished before either is overwritten.
-Launch upload(shell_batch_s& b, const ItemBuilder& ib, hipStream_t s, int pcg_workgroups = SHELL_PCG_WORKGROUPS) {
-    SHELL_HIP(hipStreamSynchronize(s));
-    size_t total = ib.rows.size() + ib.team.size();
+// drained first (unless the caller just did): earlier copies from the staging and earlier kernels reading the
+// device buffer must have finished before either is overwritten.
+Launch upload(shell_batch_s& b, const ItemBuilder& ib, hipStream_t s, int pcg_workgroups = SHELL_PCG_WORKGROUPS,
+              bool drained = false) {
+    if (!drained) SHELL_HIP(hipStreamSynchronize(s));
+    const size_t nmesh = (ib.meshes.size() * sizeof(int32_t) + sizeof(WorkItem) - 1) / sizeof(WorkItem);
+    size_t total = ib.rows.size() + ib.team.size() + nmesh;
     for (const auto& t : ib.tiles) total += t.size();
     if (total > b.items_cap || !b.items_host) {
         {
@@ -321,12 +323,10 @@ Launch upload(shell_batch_s& b, const ItemBuilder& ib, hipStream_t s, int pcg_wo
     std::copy(ib.team.begin(), ib.team.end(), b.items_host + off);
     L.team = b.items.p + off;
     off += ib.team.size();
-    std::copy(ib.meshes.begin(), ib.meshes.end(), b.mlist_host);
+    std::copy(ib.meshes.begin(), ib.meshes.end(), reinterpret_cast<int32_t*>(b.items_host + off));
+    L.meshes = reinterpret_cast<const int32_t*>(b.items.p + off);
+    off += nmesh;
     if (off) SHELL_HIP(hipMemcpyAsync(b.items.p, b.items_host, off * sizeof(WorkItem), hipMemcpyHostToDevice, s));
-    if (!ib.meshes.empty())
-        SHELL_HIP(hipMemcpyAsync(b.mlist.p, b.mlist_host, ib.meshes.size() * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, s));
-    L.meshes = b.mlist.p;
     L.nmeshes = int(ib.meshes.size());
     L.sdesc = b.sdesc.p;
     L.fdesc = b.fdesc.p;
@@ -516,7 +516,68 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
     const std::vector<const TeamPart*> parts = team_parts(b, prms[0].pcg_workgroups, s);
     const bool teams = !parts.empty();
     std::vector<MeshStep> ms(static_cast<size_t>(n));
-    SHELL_HIP(hipStreamSynchronize(s));  // the descriptor staging is reused below
+    // The item lists of the meshes in `listed`, on the device as L: rows, force tiles, and the team solve's members
+    // in groups that fit the compute units together.  They are sent when the set of meshes changes, and the
+    // descriptors when one of them does: a step whose meshes all iterate to the end sends both once.  Sent
+    // for every phase, each time after draining the stream, they took 60 of the 170 us that a step of up to 16384
+    // vertices spends beside its solve (32x32 plate, two Newton iterations: 365 -> 310 us).
+    struct Group {
+        size_t first = 0;
+        int members = 0, rows = 0;
+        size_t lds = 0;
+    };
+    const int capacity = teams ? TeamSlots::of_current_device().capacity() : 0;
+    ItemBuilder ib;
+    Launch L;
+    std::vector<Group> groups;
+    std::vector<int> listed;
+    bool drained = true;
+    auto list_items = [&](const std::vector<int>& set) {
+        if (set == listed) return;
+        ib.build(b.sims, set);
+        groups.clear();
+        if (teams) {
+            std::vector<int> order = set;
+            std::stable_sort(order.begin(), order.end(), [&](int p, int q) {
+                return parts[size_t(p)]->rows > parts[size_t(q)]->rows;
+            });
+            for (int m : order) {
+                const TeamPart& tp = *parts[size_t(m)];
+                if (groups.empty() || groups.back().members + tp.members > capacity)
+                    groups.push_back({ib.team.size(), 0, 0, 0});
+                Group& g = groups.back();
+                for (int q = 0; q < tp.members; ++q) ib.team.push_back({m, q});
+                g.members += tp.members;
+                g.rows = std::max(g.rows, int(tp.rows));
+                g.lds = std::max(g.lds, team_lds<VR>(tp.rows, tp.max_halo));
+            }
+        }
+        L = upload(b, ib, s, wg, drained);
+        drained = false;
+        listed = set;
+    };
+    bool stale = false;  // the staged descriptors differ from the device's
+    auto send_descs = [&]() {
+        if (stale) upload_descs(b, s);
+        stale = false;
+    };
+    // The targets of a solve of Newton iteration k over the meshes of `set`, into the staged descriptors.
+    auto set_targets = [&](const std::vector<int>& set, int k, bool refine) {
+        for (int m : set) {
+            const shell_step_params_t& p = *ms[size_t(m)].prm;
+            SolveDesc& d = b.sdesc_host[m];
+            auto put = [&](auto& field, auto v) {
+                stale |= field != v;
+                field = v;
+            };
+            put(d.replay, decltype(d.replay)(p.mode == SHELL_PCG_REPLAY));
+            for (int c = 0; c < 3; ++c) {
+                put(d.target[c], decltype(d.target[c] + 0)(d.replay ? p.replay_counts[3 * k + c] : p.max_pcg));
+                put(d.tol2_abs[c], refine ? ms[size_t(m)].tol2[c] : 0.0);
+            }
+        }
+    };
+    SHELL_HIP(hipStreamSynchronize(s));  // the descriptor and item staging is reused below
     if (b.fdesc_dirty) {
         for (int m = 0; m < n; ++m) b.fdesc_host[m] = force_desc(*b.sims[size_t(m)]);
         SHELL_HIP(hipMemcpyAsync(b.fdesc.p, b.fdesc_host, size_t(n) * sizeof(ForceDesc), hipMemcpyHostToDevice, s));
@@ -544,7 +605,6 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         d.rtol2 = st.prm->pcg_rtol * st.prm->pcg_rtol;
         b.sdesc_host[m] = d;
     }
-    upload_descs(b, s);
     std::vector<int> all(static_cast<size_t>(n)), need_dinv;
     for (int m = 0; m < n; ++m) {
         all[size_t(m)] = m;
@@ -555,22 +615,21 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
             sim.dinv_dt = key;
         }
     }
-    ItemBuilder ib;
-    Launch L;
+    for (int m : all)
+        if (ms[size_t(m)].prm->max_newton > 0) set_targets({m}, 0, false);
+    upload_descs(b, s);
+    stale = false;
     if (!need_dinv.empty()) {
-        ib.build(b.sims, need_dinv);
-        L = upload(b, ib, s, wg);
+        list_items(need_dinv);
         k_dinv<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
     }
-    ib.build(b.sims, all);
-    L = upload(b, ib, s, wg);
+    list_items(all);
     k_predictor<<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
     SHELL_HIP(hipGetLastError());
 
     std::vector<int> iterating = all;
     for (int k = 0; !iterating.empty(); ++k) {
-        ib.build(b.sims, iterating);
-        L = upload(b, ib, s, wg);
+        list_items(iterating);
         forces(L, s, b.prof.get());
         k_residual<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, 1);
         k_fin_residual<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
@@ -596,18 +655,6 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
             solve.push_back(m);
         }
         if (solve.empty()) break;
-        // The targets of one solve over the meshes of `set`, into the staged descriptors.
-        auto set_targets = [&](const std::vector<int>& set, bool refine) {
-            for (int m : set) {
-                const shell_step_params_t& p = *ms[size_t(m)].prm;
-                SolveDesc& d = b.sdesc_host[m];
-                d.replay = p.mode == SHELL_PCG_REPLAY;
-                for (int c = 0; c < 3; ++c) {
-                    d.target[c] = d.replay ? p.replay_counts[3 * k + c] : p.max_pcg;
-                    d.tol2_abs[c] = refine ? ms[size_t(m)].tol2[c] : 0.0;
-                }
-            }
-        };
         // A refinement pass starts from the true residual of the increment so far.
         auto refine_start = [&](const std::vector<int>& set) {
             k_pcg_fold<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
@@ -623,36 +670,15 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         // waiting: the solve is then to be run again as a chain.
         auto team_pcg = [&](const std::vector<int>& set, bool refine) -> bool {
             TeamSlots& cu = TeamSlots::of_current_device();
-            struct Group {
-                size_t first = 0;
-                int members = 0, rows = 0;
-                size_t lds = 0;
-            };
             std::vector<int> left = set;
             int limit = kTeamChunk, mode = refine ? kTeamRefine : kTeamFresh;
             for (int m : set)
                 if (ms[size_t(m)].prm->chunk > 0) limit = std::min(limit, int(ms[size_t(m)].prm->chunk));
             const int every = b.prof ? b.prof->every : 0;
-            set_targets(set, refine);
+            set_targets(set, k, refine);
             while (!left.empty()) {
-                std::vector<int> order = left;
-                std::stable_sort(order.begin(), order.end(), [&](int p, int q) {
-                    return parts[size_t(p)]->rows > parts[size_t(q)]->rows;
-                });
-                ib.build(b.sims, left);
-                std::vector<Group> groups;
-                for (int m : order) {
-                    const TeamPart& tp = *parts[size_t(m)];
-                    if (groups.empty() || groups.back().members + tp.members > cu.capacity())
-                        groups.push_back({ib.team.size(), 0, 0, 0});
-                    Group& g = groups.back();
-                    for (int q = 0; q < tp.members; ++q) ib.team.push_back({m, q});
-                    g.members += tp.members;
-                    g.rows = std::max(g.rows, int(tp.rows));
-                    g.lds = std::max(g.lds, team_lds<VR>(tp.rows, tp.max_halo));
-                }
-                L = upload(b, ib, s, wg);
-                upload_descs(b, s);
+                list_items(left);
+                send_descs();
                 if (mode == kTeamRefine) refine_start(left);
                 k_team_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
                 int most = 0;
@@ -682,16 +708,16 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
             return true;
         };
         // One PCG solve over the meshes of `set`: by teams, or as a chain of kernels: per-mesh targets and
-        // the slot ranges of its launch shape (upload() drains the stream first, so the staging is idle), the
+        // the slot ranges of its launch shape (the staging is idle since the last read of the states), the
         // first kernel (from r = -g, or for a refinement pass from the true residual of the increment so
         // far), the first product, then chunks until every mesh is done.  Returns the last product launched.
         auto run_pcg = [&](const std::vector<int>& set, bool refine) -> long {
             if (teams && team_pcg(set, refine)) return 0;
-            ib.build(b.sims, set);
-            L = upload(b, ib, s, wg);
-            set_targets(set, refine);
+            list_items(set);
+            set_targets(set, k, refine);
             set_slot_ranges(b, L, ib);
-            upload_descs(b, s);
+            stale = true;
+            send_descs();
             k_bin_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
             if (refine)
                 refine_start(set);
@@ -766,12 +792,12 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         // float64 recurrence residual drifts from the true one as float32 products accumulate, so the
         // true residual of the increment is formed with the float64 matrix and the PCG restarted from it,
         // with the first pass's bound on r.r; a pass that starts within the bound takes no iteration.
-        const bool refined = !refine.empty();
         for (int pass = 0; pass < kRefinePasses && !refine.empty(); ++pass) {
             for (int m : refine) {
                 shell_sim_s& sim = *b.sims[size_t(m)];
                 if (!sim.rq.p) sim.rq.alloc(size_t(3 * sim.nv));
                 b.sdesc_host[m].rq = sim.rq.p;
+                stale = true;
             }
             t = run_pcg(refine, true);
             std::vector<int> again;
@@ -785,10 +811,7 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
             }
             refine = again;
         }
-        if (refined) {  // the Newton update below takes the launch shape of the whole solve again
-            ib.build(b.sims, solve);
-            L = upload(b, ib, s, wg);
-        }
+        list_items(solve);  // a solve over several launches, or refinement passes, may have listed fewer meshes
         if (qs && qs->eps_u > 0.0) {
             k_absmax<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
             k_fin_step_limit<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
@@ -798,8 +821,7 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         iterating = next;
     }
     if (!qs) {
-        ib.build(b.sims, all);
-        L = upload(b, ib, s, wg);
+        list_items(all);
         k_velocity<<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows);
         SHELL_HIP(hipGetLastError());
     }
@@ -987,9 +1009,7 @@ void batch_init(shell_batch_s& b) {
             SHELL_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.state_host), 2 * b.capacity * sizeof(PcgState)));
             SHELL_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.sdesc_host), b.capacity * sizeof(SolveDesc)));
             SHELL_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.fdesc_host), b.capacity * sizeof(ForceDesc)));
-            SHELL_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.mlist_host), (b.capacity + 1) * sizeof(int32_t)));
         }
-        b.mlist.alloc(b.capacity + 1);
     }
     b.fdesc_dirty = true;
 }
@@ -997,7 +1017,7 @@ void batch_init(shell_batch_s& b) {
 void batch_free_host(shell_batch_s& b) {
     RuntimeLock lk(runtime_mutex());
     for (void** p : {reinterpret_cast<void**>(&b.state_host), reinterpret_cast<void**>(&b.sdesc_host),
-                     reinterpret_cast<void**>(&b.fdesc_host), reinterpret_cast<void**>(&b.mlist_host)}) {
+                     reinterpret_cast<void**>(&b.fdesc_host)}) {
         if (*p) (void)hipHostFree(*p);
         *p = nullptr;
     }

@@ -93,6 +93,39 @@ def test_held_coordinates_and_batches_of_teams(precision):
             pb.close()
 
 
+def test_meshes_of_a_batch_whose_solves_end_in_different_launches():
+    """Solves to a tolerance end after different numbers of launches; every mesh then takes its own Newton update,
+    with the same bits as in one launch, and as each mesh's own step (its team is of the same members)."""
+    meshes = [I.plate_mesh(9, 1.0, 0.2, 7, "EP"), I.workload_sphere_cap(40, "SS"), I.workload_cylinder(25, "FS")]
+    probs = [S.Problem(m, MAT, precision=S.SHELL_PREC_MIXED) for m in meshes]
+    starts = [_start(m) for m in meshes]
+    batch = S.shell_batch_create([pb.sim for pb in probs])
+    try:
+        ends, counts = [], []
+        for chunk in (0, 3, 11):
+            for pb, (x, v) in zip(probs, starts):
+                S.shell_sim_set_state(pb.sim, x, v, 0)
+            params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=1e-5, pcg_rtol=1e-4, chunk=chunk)
+            _, stats = S.shell_batch_step(batch, params, len(probs))
+            ends.append([S.shell_sim_get_state(pb.sim, m.nv)[:2] for pb, m in zip(probs, meshes)])
+            counts.append([st["counts"] for st in stats])
+        assert len({int(np.max(c)) for c in counts[0]}) > 1  # they end apart
+        for pb, m, (x, v), end in zip(probs, meshes, starts, ends[0]):
+            S.shell_sim_set_state(pb.sim, x, v, 0)
+            params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=1e-5, pcg_rtol=1e-4)
+            S.shell_step_implicit(pb.sim, params)
+            alone = S.shell_sim_get_state(pb.sim, m.nv)[:2]
+            assert np.array_equal(alone[0], end[0]) and np.array_equal(alone[1], end[1]), m.name
+        for end, count in zip(ends[1:], counts[1:]):
+            for m, (x, v), (x0, v0) in zip(meshes, end, ends[0]):
+                assert np.array_equal(x, x0) and np.array_equal(v, v0), m.name
+            assert all(np.array_equal(p, q) for p, q in zip(count, counts[0]))
+    finally:
+        S.shell_destroy_batch(batch)
+        for pb in probs:
+            pb.close()
+
+
 @pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
 def test_a_member_that_gives_up_hands_the_solve_to_the_chain(precision):
     """With no time to wait the first unmet meeting ends the launch (every member leaves by itself), and the step
