@@ -388,7 +388,7 @@ struct MembraneSolve {
     DevArray<int64_t> mbase;  // [nnz] base index of each CSR block
     DevArray<int64_t> mdiag;  // [nv] base index of the diagonal block
     int64_t mstride = 1;
-    DevArray<double> mval;
+    DevArray<double> mval;  // (mixed precision: mvalf)
     // staged product: rows in groups of kRowGroup, the group's directions staged in LDS.  K_s is read from
     // the bending Hessian's SELL slots and the blocks from their own SELL-64 slices (mptr, mwidth), each
     // slot's column an index into its group's list of the distinct columns of both matrices (gptr, gcols,

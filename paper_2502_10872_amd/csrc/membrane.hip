@@ -272,21 +272,32 @@ __global__ __launch_bounds__(kMsBlk) void ms_fin1(const double* __restrict__ par
 // takes the same sums in every run (no atomics, no read-modify-write).  Per triangle, with a and b the
 // corners of i and j: the Gauss-Newton part A B_a^T D_m B_b (B_c the linearised Green strain of corner
 // c: rows g_c0 F0^T, g_c1 F1^T, g_c1 F0^T + g_c0 F1^T) and the stress part A (g_a^T S+ g_b) I3.
-// Component (a, b) of CSR block e is mval[mbase[e] + (3 a + b) mstride].  With s2e (the staged layout)
-// thread t takes SELL slot t, s2e[t] its CSR block (-1 on padding, which stays zero), so that the
-// lanes of a wave write consecutive slots; otherwise thread t takes CSR block t.  Mixed precision
-// (mvalf not null) also writes the float32 copy the product reads.
-__global__ void ms_tangent(const double* __restrict__ rest, const int32_t* __restrict__ tris,
-                           const int32_t* __restrict__ brow, const int32_t* __restrict__ mcol,
-                           const int64_t* __restrict__ btptr, const int32_t* __restrict__ bttri,
-                           const int64_t* __restrict__ s2e, long nthreads, const double* __restrict__ x, double c,
-                           double nu, const int64_t* __restrict__ mbase, long mstride, double* __restrict__ mval,
-                           float* __restrict__ mvalf) {
-    const long tid = blockIdx.x * long(blockDim.x) + threadIdx.x;
-    if (tid >= nthreads) return;
-    const long e = s2e ? s2e[tid] : tid;
+// Component (a, b) of CSR block e is mval[mbase[e] + (3 a + b) mstride], in the precision the product reads.
+// The first work-groups take the diagonal blocks, one row per thread, and the rows' Jacobi entries 1 / (m + dt^2
+// (K_s,ii + tr(K_m,ii) / 3)) from them; the others the off-diagonal ones: with s2e (the staged layout) thread t
+// takes SELL slot t, s2e[t] its CSR block (-1 on padding, which stays zero), so that the lanes of a wave write
+// consecutive slots; otherwise thread t takes CSR block t.
+// What bounds it: scattered reads, a chain of five (slot, block, triangle, corners, positions) for each of the 18
+// triangles that a row's blocks visit.  The Jacobi entries in a kernel of their own, from the blocks in memory, and in
+// mixed precision the blocks in float64 too: 524 + 28 us at 1M vertices mixed, now 506 (and 500 MB less); 10 + 4 us at
+// 4096 FP64, now 10.7.
+template <typename V>
+__global__ __launch_bounds__(kMsBlk) void ms_tangent(
+    const double* __restrict__ rest, const int32_t* __restrict__ tris, const int32_t* __restrict__ brow,
+    const int32_t* __restrict__ mcol, const int64_t* __restrict__ btptr, const int32_t* __restrict__ bttri,
+    const int64_t* __restrict__ s2e, long nthreads, long nv, const double* __restrict__ x, double c, double nu,
+    const int64_t* __restrict__ mbase, const int64_t* __restrict__ mdiag, long mstride, V* __restrict__ mval,
+    const double* __restrict__ kdiag, const double* __restrict__ mass, const uint8_t* __restrict__ pinned, double dt2,
+    double* __restrict__ dinv) {
+    const long diag = (nv + kMsBlk - 1) / kMsBlk;  // work-groups of diagonal blocks
+    const bool own = long(blockIdx.x) < diag;
+    const long tid = (own ? long(blockIdx.x) : long(blockIdx.x) - diag) * kMsBlk + threadIdx.x;
+    if (tid >= (own ? nv : nthreads)) return;
+    const long at = own ? mdiag[tid] : tid;  // a component index, but for the CSR blocks off the diagonal
+    const long e = s2e ? s2e[at] : own ? at / 9 : at;
     if (e < 0) return;
     const int32_t r = brow[e], jc = mcol[e];
+    if (!own && r == jc) return;
     double acc[9];
     for (int k = 0; k < 9; ++k) acc[k] = 0.0;
     for (long q = btptr[e]; q < btptr[e + 1]; ++q) {
@@ -338,20 +349,12 @@ __global__ void ms_tangent(const double* __restrict__ rest, const int32_t* __res
         const double gsg = g[a][0] * (P00 * g[b][0] + P01 * g[b][1]) + g[a][1] * (P01 * g[b][0] + P11 * g[b][1]);
         for (int cc = 0; cc < 3; ++cc) acc[4 * cc] += A * gsg;
     }
-    const long base = s2e ? tid : mbase[e];
-    for (int k = 0; k < 9; ++k) mval[base + k * mstride] = acc[k];
-    if (mvalf)
-        for (int k = 0; k < 9; ++k) mvalf[base + k * mstride] = float(acc[k]);
-}
-
-__global__ void ms_dinv(const double* __restrict__ kdiag, const double* __restrict__ mval,
-                        const int64_t* __restrict__ mdiag, long mstride, const double* __restrict__ mass,
-                        const uint8_t* __restrict__ pinned, long nv, double dt2, double* __restrict__ dinv) {
-    long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
-    if (i >= nv) return;
-    const double* b = mval + mdiag[i];
-    const double d = mass[i] + dt2 * (kdiag[i] + (b[0] + b[4 * mstride] + b[8 * mstride]) / 3.0);
-    dinv[i] = ((pinned[i] & 7u) == 7u || d == 0.0) ? 0.0 : 1.0 / d;
+    const long base = s2e || own ? at : mbase[e];
+    for (int k = 0; k < 9; ++k) mval[base + k * mstride] = V(acc[k]);
+    if (own) {
+        const double d = mass[tid] + dt2 * (kdiag[tid] + (acc[0] + acc[4] + acc[8]) / 3.0);
+        dinv[tid] = ((pinned[tid] & 7u) == 7u || d == 0.0) ? 0.0 : 1.0 / d;
+    }
 }
 
 // r = -g, y = 0, z = D^-1 r, p = z; partials r.z, r.r
@@ -983,9 +986,10 @@ __global__ void ms_widen(const float* __restrict__ src, double* __restrict__ dst
     if (i < n) dst[i] = double(src[i]);
 }
 
-__global__ void ms_zero(double* __restrict__ p, long n) {
+template <typename V>
+__global__ void ms_zero(V* __restrict__ p, long n) {
     long i = blockIdx.x * long(blockDim.x) + threadIdx.x;
-    if (i < n) p[i] = 0.0;
+    if (i < n) p[i] = V(0);
 }
 
 inline unsigned ms_grid(long n) { return unsigned(std::max(1L, (n + kMsBlk - 1) / kMsBlk)); }
@@ -1179,8 +1183,10 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
     ms->mbase.upload(mbase.data(), mbase.size(), s);
     ms->mdiag.alloc(std::max<size_t>(mdiag.size(), 1));
     ms->mdiag.upload(mdiag.data(), mdiag.size(), s);
-    ms->mval.alloc(size_t(std::max<int64_t>(nblock_vals, 1)));
-    if (ms->mixed) ms->mvalf.alloc(size_t(std::max<int64_t>(nblock_vals, 1)));
+    if (ms->mixed)
+        ms->mvalf.alloc(size_t(std::max<int64_t>(nblock_vals, 1)));
+    else
+        ms->mval.alloc(size_t(std::max<int64_t>(nblock_vals, 1)));
     // each block's row, and the triangles holding both of its vertices, ascending (the tangent assembly's
     // fixed order): every triangle adds to the nine blocks of its corner pairs
     std::vector<int32_t> brow(size_t(std::max<int64_t>(nnz_m, 1)), 0);
@@ -1213,8 +1219,7 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
     ms->bttri.upload(bttri.data(), size_t(9 * nt), s);
     // the blocks' padding slots (staged layout) stay zero: the assembly writes every stored block
     if (ms->mval.n) ms_zero<<<ms_grid(long(ms->mval.n)), kMsBlk, 0, s>>>(ms->mval.p, long(ms->mval.n));
-    if (ms->mixed && ms->mval.n)
-        ms_narrow<<<ms_grid(long(ms->mval.n)), kMsBlk, 0, s>>>(ms->mval.p, ms->mvalf.p, long(ms->mval.n));
+    if (ms->mvalf.n) ms_zero<<<ms_grid(long(ms->mvalf.n)), kMsBlk, 0, s>>>(ms->mvalf.p, long(ms->mvalf.n));
     // per-triangle rest data
     ms->rest.alloc(size_t(std::max(5 * nt, 1L)));
     DevArray<int32_t> bad(1);
@@ -1276,21 +1281,26 @@ static void forces_at_try(shell_sim_s& sim, hipStream_t s) {
     SHELL_HIP(hipGetLastError());
 }
 
-// The membrane tangent at x into the 3x3 blocks (and their float32 copy in mixed precision), and the
+// The membrane tangent at x into the 3x3 blocks (float32 in mixed precision), and the
 // Jacobi preconditioner of M + dt^2 (K_s (x) I3 + K_m) with the given mass.
 static void tangent_at(shell_sim_s& sim, const double* x, const double* mass, double dt2, hipStream_t s) {
     shell_stencils_s& st = *sim.st;
     MembraneSolve& m = *sim.ms;
-    const long nv = sim.nv, nt = st.nt;
+    const long nv = sim.nv;
     const double c = st.young * st.thickness / (1.0 - st.poisson * st.poisson);
     const long nb = long(m.mcol.n), nthreads = m.staged ? long(m.mstride) : nb;
-    if (nt > 0 && nb > 0)
-        ms_tangent<<<ms_grid(nthreads), kMsBlk, 0, s>>>(m.rest.p, st.tris.p, m.brow.p, m.mcol.p, m.btptr.p, m.bttri.p,
-                                                        m.staged ? m.s2e.p : nullptr, nthreads, x, c, st.poisson,
-                                                        m.mbase.p, long(m.mstride), m.mval.p,
-                                                        m.mixed ? m.mvalf.p : nullptr);
-    ms_dinv<<<ms_grid(nv), kMsBlk, 0, s>>>(sim.h->kdiag.p, m.mval.p, m.mdiag.p, long(m.mstride), mass, sim.pinned.p, nv, dt2,
+    if (nv == 0) return;
+    const unsigned grid = ms_grid(nv) + ms_grid(nthreads);
+    auto launch = [&](auto* mval) {
+        ms_tangent<<<grid, kMsBlk, 0, s>>>(m.rest.p, st.tris.p, m.brow.p, m.mcol.p, m.btptr.p, m.bttri.p,
+                                           m.staged ? m.s2e.p : nullptr, nthreads, nv, x, c, st.poisson, m.mbase.p,
+                                           m.mdiag.p, long(m.mstride), mval, sim.h->kdiag.p, mass, sim.pinned.p, dt2,
                                            m.dinv.p);
+    };
+    if (m.mixed)
+        launch(m.mvalf.p);
+    else
+        launch(m.mval.p);
     SHELL_HIP(hipGetLastError());
 }
 
