@@ -212,8 +212,10 @@ __device__ __forceinline__ void lds_add_stencil(Acc& acc, const int (&vid)[K], l
 // Largest force work-group; the kernels are compiled for it, so any size up to it can be launched.
 constexpr int kMaxForceThreads = 1024;
 
-// One work-group per (mesh, vertex tile) work item.  K = 4 (edge) or 6 (triangle) vertices per stencil.
-template <int MODEL, typename R>
+// One work-group per (mesh, vertex tile) work item.  K = 4 (edge) or 6 (triangle) vertices per stencil.  CALLER: the
+// positions, forces and energy of `caller` (an instance of its own: the choice inside the stencil loop cost the
+// steps' instances 6 to 10%).
+template <int MODEL, typename R, bool CALLER>
 __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc* __restrict__ descs,
                                                    const WorkItem* __restrict__ items, long nitems,
                                                    ForceCaller caller) {
@@ -230,8 +232,8 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
     const ForceDesc& d = descs[wi.mesh];
     // global-address views of the descriptor's pointers: global loads wait on the vector-memory counter
     // only, so the LDS accumulation does not stall behind loads in flight
-    const gbl<const double>* x = G(caller.x ? caller.x : d.x);
-    const gbl<const int32_t>* cperm = caller.x ? G(caller.perm) : nullptr;
+    const gbl<const double>* x = G(CALLER && caller.x ? caller.x : d.x);
+    const gbl<const int32_t>* cperm = CALLER && caller.x ? G(caller.perm) : nullptr;
     const gbl<const double>* X = G(d.X);
     const R kb = R(d.kb), nu = R(d.nu);
     const long blk = wi.unit;
@@ -327,7 +329,7 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const long v = cperm ? cperm[in.vid[j]] : in.vid[j];
+            const long v = CALLER && cperm ? cperm[in.vid[j]] : in.vid[j];
             in.pg[j] = {x[3 * v], x[3 * v + 1], x[3 * v + 2]};
         }
         if constexpr (REST) {
@@ -497,10 +499,10 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
     }
     __syncthreads();
     const double sc = d.fscale;
-    gbl<R>* out = G(static_cast<R*>(caller.f ? caller.f : d.f));
-    const gbl<const int32_t>* perm = caller.f ? G(caller.perm) : nullptr;
+    gbl<R>* out = G(static_cast<R*>(CALLER && caller.f ? caller.f : d.f));
+    const gbl<const int32_t>* perm = CALLER && caller.f ? G(caller.perm) : nullptr;
     auto at = [&](int i) {  // where component i of the tile goes
-        return perm ? 3L * perm[base + i / 3] + i % 3 : 3 * base + i;
+        return CALLER && perm ? 3L * perm[base + i / 3] + i % 3 : 3 * base + i;
     };
     if constexpr (!MIX) {
         if (d.bias) {
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
             for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) {
                 const double bi = b[i];
                 out[at(i)] = acc.get(i) * sc + bi;
-                e_own -= bi * x[cperm ? 3L * cperm[base + i / 3] + i % 3 : 3 * base + i];
+                e_own -= bi * x[CALLER && cperm ? 3L * cperm[base + i / 3] + i % 3 : 3 * base + i];
             }
         } else {
             for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[at(i)] = R(acc.get(i) * sc);
@@ -522,7 +524,7 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
         __shared__ double sh[kMaxForceThreads / 64];
         double v[1] = {e_own};
         block_sum<1>(v, sh);
-        if (!caller.energy) {
+        if (!CALLER || !caller.energy) {
             if (threadIdx.x == 0) d.epart[blk] = v[0];
         } else if (last_block_sum(v[0], blk, nitems, d.epart, caller.arrived, sh)) {
             if (threadIdx.x == 0) *caller.energy = v[0] + caller.add;
@@ -550,21 +552,26 @@ int force_threads(Kernel kernel) {
 // A tile of 64 vertices has about 200 stencils: more than 8 threads per vertex would only start and end.
 constexpr int kForceThreadsPerVertex = 8;
 
+template <int MODEL, typename R, bool CALLER>
+void launch_instance(const ForceDesc* descs, const WorkItem* items, long nitems, int lds_T, hipStream_t s,
+                     hipEvent_t start, hipEvent_t stop, const ForceCaller& caller) {
+    static const int threads = force_threads(force_tiles<MODEL, R, CALLER>);
+    // start/stop (may be null) receive the dispatch's own begin and end times
+    hipExtLaunchKernelGGL((force_tiles<MODEL, R, CALLER>), dim3(unsigned(xcd_grid(nitems))),
+                          dim3(std::min(threads, kForceThreadsPerVertex * lds_T)),
+                          uint32_t(TileAccT<sizeof(R) == 4 ? 1 : 2>::bytes(lds_T)), s, start, stop, 0, descs, items,
+                          nitems, caller);
+    SHELL_HIP(hipGetLastError());
+}
+
 template <int MODEL>
 void launch_model(int precision, const ForceDesc* descs, const WorkItem* items, long nitems, int lds_T,
                   hipStream_t s, hipEvent_t start, hipEvent_t stop, const ForceCaller& caller) {
-    static const int threads_d = force_threads(force_tiles<MODEL, double>);
-    static const int threads_f = force_threads(force_tiles<MODEL, float>);
-    const dim3 grid(unsigned(xcd_grid(nitems)));
-    const int most = kForceThreadsPerVertex * lds_T;
-    // start/stop (may be null) receive the dispatch's own begin and end times
-    if (precision == SHELL_PREC_FP64)
-        hipExtLaunchKernelGGL(force_tiles<MODEL, double>, grid, dim3(std::min(threads_d, most)), uint32_t(TileAccT<2>::bytes(lds_T)),
-                              s, start, stop, 0, descs, items, nitems, caller);
-    else
-        hipExtLaunchKernelGGL(force_tiles<MODEL, float>, grid, dim3(std::min(threads_f, most)), uint32_t(TileAccT<1>::bytes(lds_T)),
-                              s, start, stop, 0, descs, items, nitems, caller);
-    SHELL_HIP(hipGetLastError());
+    const bool own = caller.x || caller.f;
+    auto* launch = precision == SHELL_PREC_FP64
+                       ? (own ? launch_instance<MODEL, double, true> : launch_instance<MODEL, double, false>)
+                       : (own ? launch_instance<MODEL, float, true> : launch_instance<MODEL, float, false>);
+    launch(descs, items, nitems, lds_T, s, start, stop, caller);
 }
 
 __global__ void zero_energy(double* __restrict__ out) { *out = 0.0; }

@@ -66,7 +66,8 @@ __global__ void membrane_tile_copy(const int32_t* __restrict__ src, long n, cons
 
 constexpr int kMembThreads = 512;
 
-template <typename R>
+// CALLER: the positions, forces and energy of `caller`, and the bending energies `bend` of the kernel before.
+template <typename R, bool CALLER>
 __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __restrict__ pos,
                                                                const int32_t* __restrict__ tid,
                                                                const double* __restrict__ trest,
@@ -82,15 +83,17 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
     acc.clear(3 * nown);
     const double inv_scale = acc.kUnit / scale;  // counts per force unit, a power of two: exact
     __syncthreads();
-    const int32_t* cperm = caller.x ? caller.perm : nullptr;
-    if (caller.x) pos = caller.x;
+    const int32_t* cperm = CALLER && caller.x ? caller.perm : nullptr;
+    if (CALLER && caller.x) pos = caller.x;
     double en[1] = {0.0};
     const long e0 = boff[2 * blk], e1 = boff[2 * blk + 1];
     for (long e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
         const long v[3] = {tid[4 * e], tid[4 * e + 1], tid[4 * e + 2]};
         double d1[3], d2[3];
         {
-            const long r0 = cperm ? cperm[v[0]] : v[0], r1 = cperm ? cperm[v[1]] : v[1], r2 = cperm ? cperm[v[2]] : v[2];
+            const bool through = CALLER && cperm;
+            const long r0 = through ? cperm[v[0]] : v[0], r1 = through ? cperm[v[1]] : v[1],
+                       r2 = through ? cperm[v[2]] : v[2];
             for (int i = 0; i < 3; ++i) {
                 d1[i] = pos[3 * r1 + i] - pos[3 * r0 + i];
                 d2[i] = pos[3 * r2 + i] - pos[3 * r0 + i];
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
     __syncthreads();
     R* out = f + 3 * base;
     const double sc = scale;
-    if (caller.f) {
+    if (CALLER) {
         R* cf = static_cast<R*>(caller.f);
         for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x)
             cf[3L * caller.perm[base + i / 3] + i % 3] = R(double(out[i]) + acc.get(i) * sc);
@@ -127,10 +130,10 @@ __global__ __launch_bounds__(kMembThreads) void membrane_tiles(const double* __r
         for (int i = threadIdx.x; i < 3 * nown; i += blockDim.x) out[i] = R(double(out[i]) + acc.get(i) * sc);
     }
     __shared__ double sh[kMembThreads / 64];
-    if (caller.energy)  // with the bending energy of the tile, complete since the kernel before
+    if (CALLER && caller.energy)  // with the bending energy of the tile, complete since the kernel before
         if (threadIdx.x == 0) en[0] += bend[blk];
     block_sum<1>(en, sh);
-    if (!caller.energy) {
+    if (!CALLER || !caller.energy) {
         if (threadIdx.x == 0) epart[blk] = en[0];
     } else if (last_block_sum(en[0], blk, gridDim.x, epart, caller.arrived, sh)) {
         if (threadIdx.x == 0) *caller.energy = en[0] + caller.add;
@@ -958,8 +961,9 @@ void launch_membrane_forces(shell_stencils_s& st, const double* pos, void* f, hi
     const unsigned grid = unsigned(st.nblocks);
     auto launch = [&](auto real, size_t lds) {
         using R = decltype(real);
-        membrane_tiles<R><<<grid, kMembThreads, lds, s>>>(pos, st.mtid.p, st.mtrest.p, st.mboff.p, st.nv, st.T, c,
-                                                          st.poisson, st.mscale, static_cast<R*>(f), ep, caller, bend);
+        auto* kernel = caller.f ? membrane_tiles<R, true> : membrane_tiles<R, false>;
+        kernel<<<grid, kMembThreads, lds, s>>>(pos, st.mtid.p, st.mtrest.p, st.mboff.p, st.nv, st.T, c, st.poisson,
+                                               st.mscale, static_cast<R*>(f), ep, caller, bend);
     };
     if (st.precision == SHELL_PREC_MIXED)
         launch(0.0f, TileAccT<1>::bytes(st.T));
