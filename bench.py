@@ -26,6 +26,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 
 
+RESIDENT_ROWS = dict(fp64=1024, mixed=1536)  # rows of a team's member whose matrix entries stay in registers
+
+
 def algorithmic_bytes(info: dict, hinfo: dict, precision: int, clamp_bias: bool = False) -> dict:
     """Bytes each kernel must move once (no re-reads, no SELL padding), per launch.
 
@@ -34,12 +37,10 @@ def algorithmic_bytes(info: dict, hinfo: dict, precision: int, clamp_bias: bool 
             (mixed edge plate) the tip's two float64 rest-plane coordinates; per vertex the float64 position
             read (mixed triangle plates also the rest position) and the force written; FP64 plates with
             clamped edges also read the constant clamp force per vertex.
-    spmv:   (the product kernel, which also forms the new direction p = z + beta p_old) every nonzero's
-            value and 16-bit local column id, each row group's distinct-column list, slice widths and
-            offsets, and per vertex the direction's inputs (FP64: r and D^-1; mixed: the stored float z)
-            and p_old, the mass (-1 on fixed rows, in the vector precision) read, p and q written.
-    update: per vertex p, q, y, r, D^-1 read, y and r written (mixed: z written too; y is float in mixed
-            precision, r float64 in both)."""
+    spmv:   (the product phase of a team solve's iteration) every off-diagonal entry's value and 16-bit local
+            column id; a member holds them in registers for the whole solve up to RESIDENT_ROWS rows, and the
+            vectors, the diagonal and the directions on chip always.
+    update: (its update phase) nothing but the rows on the members' borders, not counted."""
     nv, ns, k, r = info["nv"], info["ns"], info["k"], info["r"]
     shell = info["model"] in (1, 3, 5)
     mixed = precision == 1
@@ -48,12 +49,9 @@ def algorithmic_bytes(info: dict, hinfo: dict, precision: int, clamp_bias: bool 
                    + (16 if mixed and k == 4 and not shell else 0))
     force = (ns * per_stencil + nv * (24 + 3 * real) + (nv * 24 if clamp_bias and not mixed else 0)
              + (nv * 24 if mixed and k == 6 and not shell else 0))
-    ngroups = (nv + 511) // 512  # 512-row groups
-    idx = 2 if hinfo["staged"] else 4
-    direction_in = 3 * real if mixed else 24 + real
-    spmv = (hinfo["nnz"] * (real + idx) + 4 * (hinfo["group_cols"] + ngroups + 1) + 12 * hinfo["nslices"]
-            + nv * (direction_in + 3 * real + real + 3 * real + 3 * real))
-    update = nv * (3 * real + 3 * real + 3 * real + 24 + real + 3 * real + 24 + (3 * real if mixed else 0))
+    resident = nv <= 256 * RESIDENT_ROWS["mixed" if mixed else "fp64"]
+    spmv = 0 if resident else (hinfo["nnz"] - nv) * (real + 2)
+    update = 0
     return dict(force=force, spmv=spmv, update=update, force_per_stencil=per_stencil)
 
 
@@ -63,7 +61,9 @@ TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "sphere_cap_1024_ss_hbm_traffic
 TRAFFIC_SOURCES = ["paper_2502_10872_amd/csrc/spmv.hpp", "paper_2502_10872_amd/csrc/pcg_kernels.hpp",
                    "paper_2502_10872_amd/csrc/forces.hip", "paper_2502_10872_amd/csrc/host_mesh.cpp",
                    "paper_2502_10872_amd/csrc/devmath.hpp", "paper_2502_10872_amd/csrc/precompute.hip",
-                   "paper_2502_10872_amd/csrc/solver.hip", "paper_2502_10872_amd/csrc/internal.hpp"]
+                   "paper_2502_10872_amd/csrc/solver.hip", "paper_2502_10872_amd/csrc/internal.hpp",
+                   "paper_2502_10872_amd/csrc/team.hpp", "paper_2502_10872_amd/csrc/team_pcg.hpp",
+                   "paper_2502_10872_amd/csrc/hessian.hip"]
 
 
 def sources_digest(files=TRAFFIC_SOURCES) -> str:
@@ -249,21 +249,12 @@ def membrane_timing(S, I, torch, reps=20):
     return out
 
 
-MEMBRANE_STAGED_MIN_ROWS = 32768  # the library's staged membrane product from this many vertices up
-
-
 def membrane_product_bytes(nv, nnz_s, nnz_m, mixed=False):
-    """Algorithmic bytes of one coupled product launch: K_s (a column id and a value per entry), the
-    membrane tangent's 3x3 blocks (a column id and nine values per block), the values float64 (float32 in
-    mixed precision), the mass and the held mask, z and the previous direction read once, the new
-    direction and q written once (float64 vectors in both precisions).  The staged SELL layout (from
-    MEMBRANE_STAGED_MIN_ROWS vertices) has 2-byte group-local column ids, its slice offsets and the
-    groups' column lists (a few bytes per row) not counted; the CSR layout has 4-byte ids and two 8-byte
-    row offsets per row."""
+    """Algorithmic bytes of one coupled product (a phase of the team solve, whose vectors stay on chip): K_s's
+    off-diagonal entries (a 16-bit local column id and a value each), the membrane tangent's 3x3 blocks (a column id
+    and nine values), the values float64 (float32 in mixed precision), and the mass (FP64: and K_s's diagonal)."""
     real = 4 if mixed else 8
-    if nv >= MEMBRANE_STAGED_MIN_ROWS:
-        return (2 + real) * nnz_s + (2 + 9 * real) * nnz_m + nv * (8 + 1 + 48 + 48)
-    return 16 * (nv + 1) + (4 + real) * nnz_s + (4 + 9 * real) * nnz_m + nv * (8 + 1 + 48 + 48)
+    return (2 + real) * (nnz_s - nv) + (2 + 9 * real) * nnz_m + nv * (8 if mixed else 16)
 
 
 def membrane_step_timing(S, I, torch, sizes=(64, 256, 1024), steps=2):
@@ -299,7 +290,7 @@ def membrane_step_timing(S, I, torch, sizes=(64, 256, 1024), steps=2):
             halvings=[int(c[1]) for st in stats for c in st["counts"]],
             grad_ratio=[st["grad_norm"] / max(st["grad_norm0"], 1e-300) for st in stats],
             back_to_back_ms=dict(force=kt["force_ms"], product=kt["spmv_ms"], update=kt["update_ms"]),
-            product=dict(kernel="ms_iter_product_staged" if mesh.nv >= MEMBRANE_STAGED_MIN_ROWS else "ms_iter_product",
+            product=dict(kernel="ms_team_pcg (product phase)",
                          bytes_per_launch=pbytes, achieved_gbs=gbs,
                          frac=gbs / HBM_PEAK_GBS if gbs else None, nnz_s=nnz_s, blocks=nnz_m))
         pb.close()
@@ -971,7 +962,7 @@ def main(argv=None):
     ab = algorithmic_bytes(pb.info, hinfo, head)
 
     def rate(nbytes, ms):
-        return nbytes / (ms * 1e-3) / 1e9 if ms else None
+        return nbytes / (ms * 1e-3) / 1e9 if ms and nbytes else None
 
     spmv_ms = prof["product"]["avg_ms"]
     update_ms = prof["update"]["avg_ms"]
@@ -1001,11 +992,11 @@ def main(argv=None):
                              f"Newton budget {args.max_newton}, Jacobi-PCG rtol {args.pcg_rtol:g}",
                     nv=mesh.nv, stencils=pb.info["ns"], nnz=hinfo["nnz"], precision=args.precision,
                     parallelism="single GPU"),
-        roofline=dict(bound="hbm", kernel="k_pcg_spmv (PCG state, direction update, 3-column SELL-64 product)",
+        roofline=dict(bound="hbm", kernel="k_team_pcg (product phase: PCG state, direction update, 3-column product)",
                       achieved=spmv_gbs, peak=HBM_PEAK_GBS, unit="GB/s",
                       frac=spmv_gbs / HBM_PEAK_GBS if spmv_gbs else None, traffic=traffic_spmv,
                       bytes_per_launch=ab["spmv"], avg_ms=spmv_ms, sampled_launches=prof["product"]["count"]),
-        update_kernel=dict(kernel="k_pcg_update", achieved_gbs=update_gbs,
+        update_kernel=dict(kernel="k_team_pcg (update phase: on chip)", achieved_gbs=update_gbs,
                            frac=update_gbs / HBM_PEAK_GBS if update_gbs else None, bytes_per_launch=ab["update"],
                            avg_ms=update_ms, traffic=traffic_update),
         force_kernel=dict(kernel="force_tiles", stencils_per_s=stencils_per_s, achieved_gbs=force_gbs,
