@@ -1544,7 +1544,7 @@ struct DeviceReady {
     void await_resume() const noexcept {}
 };
 
-// co_await Later{}: suspend until the driver comes round again (what the step waits for is no event)
+// co_await Later{}: suspend until the loop over the members comes round again (what the step waits for is no event)
 struct Later {
     bool await_ready() const noexcept { return false; }
     void await_suspend(StepTask::Handle h) const noexcept { h.promise().wait = nullptr; }

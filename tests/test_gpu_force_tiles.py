@@ -120,3 +120,34 @@ def test_operator_product_over_its_inputs(model, n, flags):
         S.shell_hessian_apply(pb.h, md, 0.25, pd, q)
         torch.cuda.synchronize()
         assert torch.equal(both.view(mesh.nv, 3), q)
+
+
+@pytest.mark.parametrize("model,n,flags", [("SS", 40, 0), ("ES", 90, S.SHELL_FLAG_MEMBRANE)])
+def test_captured_forces_and_products_replay(model, n, flags):
+    """Replays of a captured evaluation and product on new positions, with eager calls between them, equal the
+    eager results bit for bit (the arrival counters are back at zero after every launch)."""
+    mesh = I.workload_sphere_cap(n, model)
+    with S.Problem(mesh, I.MATERIAL, model=model, flags=flags) as pb:
+        x = torch.as_tensor(mesh.X, device="cuda").clone()
+        f, q = torch.empty_like(x), torch.empty_like(x)
+        e = torch.zeros(1, device="cuda", dtype=torch.float64)
+
+        def run(f, e, q):
+            S.shell_eval_forces(pb.st, x, f, e)
+            S.shell_hessian_apply(pb.h, None, 0.5, x, q)
+
+        run(f, e, q)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run(f, e, q)
+        f2, q2, e2 = torch.empty_like(f), torch.empty_like(q), torch.empty_like(e)
+        for k in range(4):
+            x.copy_(torch.as_tensor(mesh.X + 1e-3 * mesh.spacing * I.rng(k).standard_normal(mesh.X.shape)))
+            run(f2, e2, q2)
+            f.fill_(float("nan"))
+            q.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(f, f2) and torch.equal(q, q2) and torch.equal(e, e2)
