@@ -616,6 +616,9 @@ shell_status_t shell_sim_create(shell_stencils_t st, shell_hessian_t h, const do
         sim->x.upload(xi.data(), xi.size(), s);
         sim->v.upload(vi.data(), vi.size(), s);
         sim->pinned.upload(pi.data(), pi.size(), s);
+        const std::vector<uint32_t> zeros(arrival_counters((nv + kRowGroup - 1) / kRowGroup), 0u);
+        sim->arrived.alloc(zeros.size());
+        sim->arrived.upload(zeros.data(), zeros.size(), s);
         sim_mass(*sim, s);
         SHELL_HIP(hipStreamSynchronize(s));
         if (nv > 0 && membrane) {
@@ -948,7 +951,7 @@ shell_status_t shell_sim_device_bytes(shell_sim_t sim, int64_t* stencil_bytes, i
         for (size_t v : {sim->x.bytes(), sim->v.bytes(), sim->xt.bytes(), sim->xhat.bytes(), sim->g.bytes(),
                          sim->mass.bytes(), sim->y.bytes(), sim->r.bytes(), sim->f.bytes(), sim->dinv.bytes(), sim->mq.bytes(),
                          sim->pinned.bytes(), sim->p.bytes(), sim->p2.bytes(), sim->z.bytes(), sim->q.bytes(),
-                         sim->bins.bytes(), sim->slots.bytes(), sim->partials.bytes(), sim->y64.bytes(), sim->rq.bytes(),
+                         sim->bins.bytes(), sim->slots.bytes(), sim->arrived.bytes(), sim->partials.bytes(), sim->y64.bytes(), sim->rq.bytes(),
                          sim->zmass.bytes(), sim->fext.bytes(), sim->ustep.bytes()})
             c += int64_t(v);
         if (sim->ms) c += int64_t(sim->ms->bytes());

@@ -251,6 +251,7 @@ struct SolveDesc {
     const uint16_t* lcol;
     PcgState* st;                   // two states: st[t & 1] enters PCG iteration t
     double* part;                   // reduction partials, quantity-major [q][group]
+    uint32_t* arrived;              // arrival counters of the residual norm, at zero between launches
     double* bins;                   // PCG dot-product partials [parity][set][quantity][work-group slot]
     int32_t pq_lo, pq_hi;           // logical work-groups of the product launch that can touch this mesh
     int32_t rz_lo, rz_hi;           // the same for the update launch (and the solve's first kernel)
@@ -478,6 +479,7 @@ struct shell_sim_s {
     shell::DevArray<float> z;            // mixed only: the preconditioned residual, read by the product
     shell::DevArray<double> bins;        // PCG dot-product bins
     shell::DevArray<double> slots;       // team solve: the members' sums
+    shell::DevArray<uint32_t> arrived;   // arrival counters of the residual norm
     shell::DevArray<double> partials;    // reduction partials
     // quasi-static solves only: zero mass, the applied load (internal order), the Newton step's scale
     shell::DevArray<double> zmass, fext, ustep;

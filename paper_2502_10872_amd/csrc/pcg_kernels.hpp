@@ -8,6 +8,7 @@
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
+#include "team.hpp"
 
 namespace shell {
 
@@ -15,7 +16,7 @@ namespace {
 
 
 constexpr int kBlk = kRowGroup;  // rows per work item (one row per thread)
-constexpr int kRedBlk = 512;  // residual-norm kernel: one work-group per mesh
+constexpr int kRedBlk = 512;  // kernels of one work-group per mesh
 constexpr int kMaxPart = 8;   // partial quantities per work-group (buffer sized kMaxPart * groups)
 
 inline long blocks(long n) { return (n + kBlk - 1) / kBlk; }
@@ -43,19 +44,6 @@ constexpr int kFoldIters = 16;
 // exactly (solution error 2e-7 on the same system).  The float64 matrix keeps the plain form.
 template <typename MR>
 constexpr bool kDiffForm = sizeof(MR) == 4;
-
-// fixed-order sum of NQ partials over ngroups work-groups; result in thread 0's out[]
-template <int NQ>
-__device__ void reduce_partials(const double* __restrict__ part, long ngroups, double (&out)[NQ]) {
-    __shared__ double sh[NQ * (kRedBlk / 64)];
-    for (int q = 0; q < NQ; ++q) out[q] = 0.0;
-    // partials are stored quantity-major, part[q * ngroups + group], so these loads coalesce
-#pragma unroll 4
-    for (long b = threadIdx.x; b < ngroups; b += kRedBlk)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) out[q] += part[q * ngroups + b];
-    block_sum<NQ>(out, sh);
-}
 
 // this work-group's (mesh, row group); false if the grid slot is idle
 __device__ __forceinline__ bool work_item(const WorkItem* __restrict__ items, long nitems, WorkItem& wi) {
@@ -169,7 +157,8 @@ __global__ __launch_bounds__(kBlk) void k_dinv(const SolveDesc* __restrict__ des
 }
 
 // g = M (x - x_hat) - dt^2 (f + F), fixed rows zero (F: the quasi-static load, absent in a time step);
-// partial |g|^2
+// |g|^2 by the mesh's last work-group, which also readies the slots of the coming team solve (kernels of
+// their own, one work-group per mesh, took 8 us of a small step's Newton iteration)
 template <typename VR>
 __global__ __launch_bounds__(kBlk) void k_residual(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items, long nitems,
                            int from_xhat) {
@@ -193,18 +182,12 @@ __global__ __launch_bounds__(kBlk) void k_residual(const SolveDesc* __restrict__
     }
     __shared__ double sh[kBlk / 64];
     block_sum<1>(acc, sh);
-    if (threadIdx.x == 0) d.part[wi.unit] = acc[0];
-}
-
-// |g|^2 of each mesh
-__global__ __launch_bounds__(kRedBlk) void k_fin_residual(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ meshes) {
-    const SolveDesc& d = descs[meshes[blockIdx.x]];
-    double tot[1];
-    reduce_partials<1>(d.part, d.ngroups, tot);
+    if (!last_block_sum(acc[0], wi.unit, d.ngroups, d.part, d.arrived, sh)) return;
     if (threadIdx.x == 0) {
-        d.st[0].gsq = tot[0];
-        d.st[0].nonfinite = !isfinite(tot[0]);
+        d.st[0].gsq = acc[0];
+        d.st[0].nonfinite = !isfinite(acc[0]);
     }
+    if (d.slots) team_clear(d.slots, &d.st[0].gone, d.tmembers);
 }
 
 // zeroes the dot-product partials of the coming solve

@@ -404,6 +404,7 @@ SolveDesc solve_desc(shell_sim_s& sim, PcgState* st, const TeamPart* tp = nullpt
     d.lcol = sim.h->lcol.p;
     d.st = st;
     d.part = sim.partials.p;
+    d.arrived = sim.arrived.p;
     d.bins = sim.bins.p;
     d.nv = sim.nv;
     d.ngroups = blocks(sim.nv);
@@ -632,7 +633,6 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         list_items(iterating);
         forces(L, s, b.prof.get());
         k_residual<VR><<<xcd_grid(L.nrows), kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, 1);
-        k_fin_residual<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
         SHELL_HIP(hipGetLastError());
         read_states(b, s);
         std::vector<int> solve;
@@ -680,7 +680,8 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
                 list_items(left);
                 send_descs();
                 if (mode == kTeamRefine) refine_start(left);
-                k_team_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
+                if (mode != kTeamFresh)  // the residual's kernel has readied a first launch's slots
+                    k_team_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
                 int most = 0;
                 for (const Group& g : groups) most = std::max(most, g.members);
                 {
@@ -874,7 +875,6 @@ void time_impl(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out,
         // a residual from the current forces, then an always-active recurrence through its first update
         forces(L, s);
         k_residual<VR><<<grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, 0);
-        k_fin_residual<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
         k_bin_clear<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
         k_pcg_init<VR><<<L.upd_grid, kBlk, 0, s>>>(L.sdesc, L.rows, L.nrows, L.per_u);
         k_pcg_spmv<VR, MR><<<L.pcg_grid, kBlk, L.lds_spmv, s>>>(L.sdesc, L.rows, L.nrows, 0, L.per);
