@@ -4,7 +4,7 @@
 // work-group owns one tile and walks the list of every stencil that touches the tile (stencils on a
 // tile boundary appear in each tile they touch).  Each stencil's force on the tile's own vertices is
 // added into a float64 LDS accumulator; contributions to other tiles' vertices are left to those
-// tiles.  The tile is then written to HBM once: no global atomics, no zero-fill, one coalesced store
+// tiles.  The tile is then written to HBM once: no global atomics, no zero-fill, one store
 // per vertex.  The accumulation is exact in fixed-point parts (TileAcc), so its result does not depend
 // on the order in which the waves add.  Stencil data is streamed in blocks of 64 stencils, in 16-byte chunks of fields (a
 // wave's 64 loads of one chunk are one contiguous 1 KB run, so every load is coalesced and a wave
