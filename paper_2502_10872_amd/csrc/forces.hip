@@ -549,8 +549,11 @@ int force_threads(Kernel kernel) {
     return std::min(kMaxForceThreads, 256 * std::max(1, waves / 2));
 }
 
-// A tile of 64 vertices has about 200 stencils: more than 8 threads per vertex would only start and end.
+// A tile of 64 vertices has about 200 stencils: more than 8 threads per vertex would only start and end.  Rounded up
+// to multiples of 256 like the sizes above (a tile may have any number of vertices): the energy sums count whole waves,
+// and 800 threads for 100 vertices lost what the last half wave held.
 constexpr int kForceThreadsPerVertex = 8;
+inline int tile_threads(int threads, int T) { return std::min(threads, (kForceThreadsPerVertex * T + 255) / 256 * 256); }
 
 template <int MODEL, typename R, bool CALLER>
 void launch_instance(const ForceDesc* descs, const WorkItem* items, long nitems, int lds_T, hipStream_t s,
@@ -558,7 +561,7 @@ void launch_instance(const ForceDesc* descs, const WorkItem* items, long nitems,
     static const int threads = force_threads(force_tiles<MODEL, R, CALLER>);
     // start/stop (may be null) receive the dispatch's own begin and end times
     hipExtLaunchKernelGGL((force_tiles<MODEL, R, CALLER>), dim3(unsigned(xcd_grid(nitems))),
-                          dim3(std::min(threads, kForceThreadsPerVertex * lds_T)),
+                          dim3(tile_threads(threads, lds_T)),
                           uint32_t(TileAccT<sizeof(R) == 4 ? 1 : 2>::bytes(lds_T)), s, start, stop, 0, descs, items,
                           nitems, caller);
     SHELL_HIP(hipGetLastError());

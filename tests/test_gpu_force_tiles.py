@@ -6,6 +6,8 @@ same integers per vertex whatever the tile, so the forces agree bit for bit.  Th
 is summed per tile in float64: with E the sum of some 1e5 terms of one sign the two groupings differ by less
 than 1e-12 of it."""
 
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -151,3 +153,45 @@ def test_captured_forces_and_products_replay(model, n, flags):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(f, f2) and torch.equal(q, q2) and torch.equal(e, e2)
+
+
+def _same_energy_as_tiles_of_2048(mesh, x, precision, block, reorder):
+    out = []
+    for T in (block, 2048):
+        with S.Problem(mesh, I.MATERIAL, model="EP", precision=precision, block_vertices=T, reorder=reorder,
+                       sim=False) as pb:
+            xd = torch.as_tensor(x, device="cuda")
+            f = torch.empty(mesh.nv, 3, device="cuda",
+                            dtype=torch.float32 if precision == S.SHELL_PREC_MIXED else torch.float64)
+            e = torch.zeros(2, device="cuda", dtype=torch.float64)
+            S.shell_eval_forces(pb.st, xd, f, e)
+            S.shell_eval_forces_noalloc(pb.st, xd, f, e[1:])
+            torch.cuda.synchronize()
+            out.append((f.cpu().numpy(), e.cpu().numpy()))
+    (f, e), (fw, ew) = out
+    assert np.array_equal(f, fw)
+    assert np.all(np.abs(e - ew) <= 1e-12 * np.abs(ew))
+
+
+# eight threads per vertex of these are no whole number of waves; more tiles than threads in a work-group, so that
+# every thread of the last work-group has partials to add
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("block", [65, 90, 100, 127])
+def test_energy_of_tiles_of_any_size(block, precision):
+    mesh = I.plate_mesh(400, 1.0, 0.2, 7, "EP")
+    x = mesh.X + 1e-3 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
+    _same_energy_as_tiles_of_2048(mesh, x, precision, block, 1)
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("block", [65, 100])
+def test_energy_of_tiles_with_more_stencils_than_threads(block, precision):
+    """Vertices numbered at random: a tile's vertices are no neighbours, and its list holds about twelve stencils
+    per vertex, so that every thread of its work-group takes some."""
+    mesh = I.plate_mesh(40, 1.0, 0.2, 7, "EP")
+    new = I.rng(5).permutation(mesh.nv)
+    old = np.argsort(new)
+    mesh = dataclasses.replace(mesh, X=mesh.X[old].copy(), tris=new[mesh.tris].astype(mesh.tris.dtype),
+                               pinned=mesh.pinned[old].copy())
+    x = mesh.X + 1e-3 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
+    _same_energy_as_tiles_of_2048(mesh, x, precision, block, 0)
