@@ -187,7 +187,9 @@ shell_status_t shell_stencils_export(shell_stencils_t st, int32_t* idx, double* 
  * Shells: the corotational gradient with the current stencil normal (eqs 24-26, 43-45, 55-57;
  * normal gradients App. B).  x device [nv][3] float64; f device [nv][3], float64 for
  * SHELL_PREC_FP64 stencils and float32 for SHELL_PREC_MIXED, overwritten.  energy: device float64
- * scalar receiving the bending energy, or NULL.  Asynchronous on `stream`.
+ * scalar receiving the bending energy, or NULL.  Asynchronous on `stream`.  The handle holds the call's energy
+ * partials and staging: evaluations of one handle must not overlap on the device (on two streams), where they
+ * spoil each other's results, though no later call's.
  */
 shell_status_t shell_eval_forces(shell_stencils_t st, const double* x, void* f, double* energy,
                                  shell_stream_t stream);

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "arrivals.hpp"
+
 namespace shell {
 
 template <typename R>
@@ -152,28 +154,15 @@ __device__ __forceinline__ void block_sum(double (&v)[NQ], double* sh) {
 // The last of n work-groups to arrive sums the n partials of all of them in a fixed order, so that a total
 // needs no kernel of its own.  `mine` is this work-group's partial (thread 0), stored to part[blk]; every thread
 // calls it.  True in the last work-group, with the total in thread 0's `mine`; the counters are back at zero then.
-// Work-groups arrive in groups of 16, the last of a group at the root, because adds to one address pass one at a
-// time: 512 work-groups that finish together spent 5 us on one counter, and spend 2 us on 33.
-constexpr int kArriveGroup = 16, kArriveStride = 32;  // counters lie in cache lines of their own
-__host__ __device__ constexpr size_t arrival_counters(long n) {
-    return size_t(kArriveStride) * size_t(1 + (n + kArriveGroup - 1) / kArriveGroup);
-}
 __device__ __forceinline__ bool last_block_sum(double& mine, long blk, long n, double* part, uint32_t* arrived,
                                                double* sh) {
     __shared__ int last;
     if (threadIdx.x == 0) {
         agent_store(part + blk, mine);
         wait_stores();  // the partial is in memory before the arrival is
-        auto arrive = [](uint32_t* counter, long members) {
-            if (__hip_atomic_fetch_add(G(counter), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) !=
-                uint32_t(members - 1))
-                return false;
-            agent_store(counter, 0u);
-            return true;
-        };
-        const long g = blk / kArriveGroup, groups = (n + kArriveGroup - 1) / kArriveGroup;
-        last = arrive(arrived + kArriveStride * (1 + g), min(long(kArriveGroup), n - g * kArriveGroup)) &&
-               (groups == 1 || arrive(arrived, groups));
+        last = arrive_last(arrived, blk, n, [](uint32_t* counter, uint32_t top) {
+            return __builtin_amdgcn_atomic_inc32(G(counter), top, __ATOMIC_RELAXED, "agent");
+        });
     }
     __syncthreads();
     if (!last) return false;

@@ -195,3 +195,38 @@ def test_energy_of_tiles_with_more_stencils_than_threads(block, precision):
                                pinned=mesh.pinned[old].copy())
     x = mesh.X + 1e-3 * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape)
     _same_energy_as_tiles_of_2048(mesh, x, precision, block, 0)
+
+
+def test_energies_after_evaluations_that_overlapped():
+    """Evaluations of one handle on several streams at a time spoil each other's energies, which the caller is told not
+    to do; the handle's later ones are right all the same.  Captured, so that they follow one another closely enough
+    to overlap; 32 tiles, so that an evaluation is little more than its arrivals."""
+    mesh = I.workload_sphere_cap(45, "SS")
+    states = [mesh.X + a * mesh.spacing * I.rng(3).uniform(-1, 1, mesh.X.shape) for a in (1e-3, 2e-3, 3e-3, 4e-3)]
+    with S.Problem(mesh, I.MATERIAL, sim=False) as pb:
+        xd = torch.as_tensor(states[0], device="cuda").clone()
+        f, e = torch.empty_like(xd), torch.zeros(1, device="cuda", dtype=torch.float64)
+
+        def energies():  # at other positions each, so that no partial of an earlier call will do
+            out = []
+            for x in states:
+                xd.copy_(torch.as_tensor(x))
+                S.shell_eval_forces(pb.st, xd, f, e)
+                torch.cuda.synchronize()
+                out.append(float(e))
+            return out
+
+        want = energies()
+        lanes = []
+        for _ in range(4):
+            fs, es, graph = torch.empty_like(xd), torch.zeros_like(e), torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                for _ in range(50):
+                    S.shell_eval_forces(pb.st, xd, fs, es)
+            lanes.append((torch.cuda.Stream(), graph, fs, es))
+        for _ in range(40):
+            for s, graph, _, _ in lanes:
+                with torch.cuda.stream(s):
+                    graph.replay()
+        torch.cuda.synchronize()
+        assert energies() == want

@@ -1,0 +1,19 @@
+"""Host and device logic that needs no device, compiled from the library's own headers with the host compiler."""
+
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2502_10872_amd", "csrc")
+
+
+def run_host(tmp_path, name, *args):
+    exe = str(tmp_path / name)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-pthread", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe], check=True)
+    done = subprocess.run([exe, *args], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0 and done.stdout.strip().endswith("ok"), done.stdout + done.stderr
+
+
+def test_arrival_counters_return_to_zero(tmp_path):
+    run_host(tmp_path, "arrivals")
