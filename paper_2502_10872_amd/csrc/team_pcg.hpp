@@ -173,6 +173,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team_pcg(const SolveDesc* __re
                 o.iters[c] = q.iters[c];
                 o.active[c] = q.active[c];
                 o.budget[c] = q.budget;
+                o.nonfinite[c] = q.nonfinite;
             }
         }
         rec[0] = o;

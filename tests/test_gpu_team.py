@@ -187,3 +187,22 @@ def test_a_membrane_solve_over_several_launches_is_the_same_solve(precision):
             rc, st = S.shell_step_implicit(pb.sim, params)
             out.append((st["counts"], *S.shell_sim_get_state(pb.sim, mesh.nv)[:2]))
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+def test_a_column_that_goes_non_finite_is_reported_whatever_the_launches():
+    """A load that is finite in float64 and overflows float32: its column of the solve is lost in the first iteration,
+    while the others iterate on.  The solve ends as non-finite, without a Newton update, in one launch and over
+    several."""
+    mesh = I.workload_cylinder(40, "SS")
+    load = 1e-3 * I.rng(3).standard_normal((mesh.nv, 3))
+    load[np.flatnonzero(mesh.pinned == 0)[100], 0] = 1e45
+    out = []
+    with S.Problem(mesh, MAT, precision=S.SHELL_PREC_MIXED) as pb:
+        for chunk in (0, 1, 3):
+            S.shell_sim_set_state(pb.sim, mesh.X, np.zeros_like(mesh.X), 0)
+            with pytest.raises(S.ShellError, match="NONFINITE"):
+                S.shell_solve_static(pb.sim, load, max_newton=2, pcg_rtol=1e-5, chunk=chunk)
+            st = S.shell_sim_get_stats(pb.sim)
+            assert np.isfinite(st["grad_norm0"])  # the solve was reached
+            out.append(st["newton_iters"])
+    assert out == [0, 0, 0]
