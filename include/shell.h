@@ -276,8 +276,9 @@ typedef struct {
     int32_t chunk;         /* PCG iterations launched between host convergence checks; 0 = default */
     int32_t pcg_workgroups; /* 0 = default: a solve is one launch of resident work-groups where the mesh allows it,
                                else a chain of kernels of 512 work-groups; 1..1024: the chain, with this many
-                               work-groups per kernel (each takes consecutive 512-row groups).  Batches use
-                               the first entry's value */
+                               work-groups per kernel (each takes consecutive 512-row groups; with the membrane
+                               the chain's kernels choose their own number).  Batches use the first entry's
+                               value (with the membrane each member its own) */
     int32_t flags;         /* 0 or SHELL_STEP_NO_GRAPHS; batches use the first entry's value */
     const int32_t* replay_counts; /* host [max_newton][3], REPLAY only: exact PCG iterations */
 } shell_step_params_t;

@@ -1617,10 +1617,10 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
         // the membrane tangent and the Jacobi preconditioner
         tangent_at(sim, sim.x.p, sim.mass.p, dt2, s);
         // one PCG over all coordinates: by a team, launched once all its members' compute units are free, or
-        // (no team, or a member gave up waiting) as a chain of kernels
+        // (no team, the chain asked for by its work-groups, or a member gave up waiting) as a chain of kernels
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
-        if (m.tpart) {
+        if (m.tpart && p.pcg_workgroups == 0) {
             const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
             TeamSlots& cu = TeamSlots::of_current_device();
             for (bool resume = false; !solved; resume = true) {
@@ -1830,7 +1830,7 @@ shell_status_t membrane_static(shell_sim_s& sim, const shell_step_params_t& p, c
         tangent_at(sim, sim.x.p, sim.zmass.p, 1.0, s);
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
-        if (m.tpart) {
+        if (m.tpart && p.pcg_workgroups == 0) {
             const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
             for (bool resume = false; !solved; resume = true) {
                 TeamLease lease(TeamSlots::of_current_device(), m.tpart->members);

@@ -206,3 +206,48 @@ def test_a_column_that_goes_non_finite_is_reported_whatever_the_launches():
             assert np.isfinite(st["grad_norm0"])  # the solve was reached
             out.append(st["newton_iters"])
     assert out == [0, 0, 0]
+
+
+def _membrane_run(mesh, x, v, precision, ticks=2 ** 64 - 1, wg=0, flags=0, step_flags=0, static=False, held=None):
+    counts = np.zeros((2, 3), np.int32)
+    counts[:, 0] = 20
+    with S.Problem(mesh, MAT, precision=precision, flags=S.SHELL_FLAG_MEMBRANE | flags, held=held) as pb:
+        _no_waiting(pb.sim, ticks)
+        S.shell_sim_set_state(pb.sim, x, v, 0)
+        if static:
+            load = 1e-6 * I.rng(3).standard_normal((mesh.nv, 3))
+            S.shell_solve_static(pb.sim, load, max_newton=2, replay=counts, pcg_workgroups=wg, flags=step_flags)
+        else:
+            params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=0.0, replay=counts, pcg_workgroups=wg,
+                                          flags=step_flags)
+            S.shell_step_implicit(pb.sim, params)
+        return S.shell_sim_get_state(pb.sim, mesh.nv)[:2]
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+def test_the_membrane_chain_asked_for_is_the_chain(precision, static):
+    """`pcg_workgroups` selects the chain of kernels with the membrane too: the same bits as a team that hands its
+    solve over, from captured graphs and launched one by one."""
+    mesh = I.workload_cylinder(60, "SS")
+    x, v = _start(mesh)
+    want = _membrane_run(mesh, x, v, precision, ticks=0, static=static)
+    for wg, step_flags in ((1, 0), (512, 0), (512, S.SHELL_STEP_NO_GRAPHS)):
+        got = _membrane_run(mesh, x, v, precision, wg=wg, step_flags=step_flags, static=static)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("precision", [S.SHELL_PREC_FP64, S.SHELL_PREC_MIXED])
+@pytest.mark.parametrize("model,n", [("SS", 5), ("FS", 8), ("ES", 22), ("SS", 23)])
+def test_membrane_solves_of_one_member_equal_the_kernel_chain_and_the_direct_product(model, n, precision):
+    """A team of one member never waits and so never hands over (up to 512 vertices; 23 x 23 has three members): the
+    chain is asked for.  The direct product's solve of such a mesh is the one of a single work-group over CSR rows (16, 8
+    and 4 lanes each; at 23 x 23 its own chain).  Bounds as above."""
+    mesh = I.workload_cylinder(n, model)
+    x, v = _start(mesh)
+    held = np.arange(mesh.nv) % 5 * (np.arange(mesh.nv) % 11 == 0)
+    xa, va = _membrane_run(mesh, x, v, precision, held=held)
+    bound = 1e-10 if precision == S.SHELL_PREC_FP64 else 1e-6
+    for wg, flags in ((512, 0), (0, S.SHELL_FLAG_DIRECT_PRODUCT)):
+        xb, vb = _membrane_run(mesh, x, v, precision, wg=wg, flags=flags, held=held)
+        assert rel(xa - mesh.X, xb - mesh.X) <= bound and rel(va, vb) <= bound
