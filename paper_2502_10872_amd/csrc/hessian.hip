@@ -10,6 +10,7 @@
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
+#include "team_host.hpp"
 
 namespace shell {
 
@@ -232,22 +233,11 @@ void launch_assemble(shell_hessian_s& h, hipStream_t s) {
     SHELL_HIP(hipStreamSynchronize(s));  // temporaries are released on return
 }
 
-// Rows per member of a simulation on its own.  One member up to 1024 rows (no meetings: 6.8 us per iteration
-// against 7.5 with two members of 512); then few rows each, since an iteration's product is a chain of
-// latencies that grows with a member's rows: 256 while one wave can read all members' sums (4225 rows: 7.6 us
-// against 8.5 with 512 and 10.5 with 1024), 512 up to as many members as compute units (32761 rows: 9.5 us
-// against 10.4 with 256), beyond that whatever keeps one member per unit.
-int64_t team_rows(int64_t nv) {
-    if (nv > 1024 && nv <= 64 * 256) return 256;
-    return team_rows_spread(nv, 1024, 512);
-}
-
-int64_t team_rows_spread(int64_t nv, int64_t alone, int64_t least) {
+int compute_units() {
     int dev = 0, cus = 0;
     SHELL_HIP(hipGetDevice(&dev));
     SHELL_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    auto whole = [](int64_t n) { return (n + 63) / 64 * 64; };
-    return nv <= alone ? whole(nv) : std::max(least, whole((nv + cus - 1) / cus));
+    return cus;
 }
 
 std::unique_ptr<TeamPart> build_part(shell_hessian_s& h, int64_t R, size_t real, hipStream_t s,
@@ -334,10 +324,12 @@ static void build_team_values(shell_hessian_s& h, hipStream_t s) {
 }
 
 void build_team(shell_hessian_s& h, hipStream_t s) {
-    if (!h.pat.nv || team_rows(h.pat.nv) > kTeamMaxRows) return;
+    if (!h.pat.nv) return;
+    const int64_t rows = team_rows(h.pat.nv, compute_units());
+    if (rows > kTeamMaxRows) return;
     build_team_values(h, s);
     if (h.st->cfg_flags & SHELL_FLAG_MEMBRANE) return;  // its solver's part covers the tangent's columns too
-    auto part = build_part(h, team_rows(h.pat.nv), h.valf.p ? sizeof(float) : sizeof(double), s);
+    auto part = build_part(h, rows, h.valf.p ? sizeof(float) : sizeof(double), s);
     if (part) {
         h.parts.push_back(std::move(part));
         return;

@@ -601,9 +601,8 @@ void launch_assemble(shell_hessian_s& h, hipStream_t s);
 // perm: q in the caller's order; through (staged patterns only): p and mass in it too
 void launch_apply(const shell_hessian_s& h, const double* mass, double dt2, const double* p, double* q,
                   hipStream_t s, const int32_t* perm = nullptr, bool through = false);
-// rows per member of a mesh on its own; one member up to `alone` rows, then one per compute unit, of `least` rows
-int64_t team_rows(int64_t nv);
-int64_t team_rows_spread(int64_t nv, int64_t alone, int64_t least);
+// compute units of the current device
+int compute_units();
 // The part with members of R rows, or null where it does not fit: each member's halo (the columns of its rows
 // that are other members' rows, ascending; `lists` receives them), the rows that others read, and the pairs'
 // local columns.  real: bytes of a direction's component in LDS.  row2, col2: a second pattern (CSR) whose

@@ -1046,10 +1046,7 @@ void membrane_sim_init(shell_sim_s& sim, hipStream_t s) {
     ms->mcol.upload(mcol.data(), mcol.size(), s);
     // the deal of the rows for the team solve (its members read K_s's columns and the blocks')
     std::vector<std::vector<int32_t>> halo;
-    // rows per member: one member up to 512, then as many members as compute units, of at least 256 rows (an
-    // iteration reads four times the matrix of the bending solve, so the rows are dealt out sooner: 65536 rows 15.6
-    // us with 256, 16.2 with 512; 128 rows gain 8% at 1089 and lose 10% at 16384)
-    const int64_t R = nv > 0 ? team_rows_spread(nv, 512, 256) : 0;
+    const int64_t R = nv > 0 ? team_rows_membrane(nv, compute_units()) : 0;
     if ((st.cfg_flags & SHELL_FLAG_DIRECT_PRODUCT) == 0 && nv > 0)
         ms->tpart = build_part(h, R, sizeof(double), s, &mrow, &mcol, &halo);
     // where each block is stored: CSR order (the direct product), or SELL-64 slices for the staged one

@@ -77,10 +77,7 @@ GraphCache::~GraphCache() {
 
 void TeamSlots::ensure() {
     if (capacity_) return;
-    int dev = 0;
-    SHELL_HIP(hipGetDevice(&dev));
-    SHELL_HIP(hipDeviceGetAttribute(&capacity_, hipDeviceAttributeMultiprocessorCount, dev));
-    free_ = capacity_;
+    capacity_ = free_ = compute_units();
 }
 
 TeamSlots& TeamSlots::of_current_device() {
@@ -95,12 +92,14 @@ TeamSlots& TeamSlots::of_current_device() {
 }
 
 void TeamSlots::acquire(int n) {
+    SHELL_CHECK(n <= capacity_, SHELL_E_UNSUPPORTED, "a team with more members than the device has compute units");
     std::unique_lock<std::mutex> lk(m_);
     cv_.wait(lk, [&] { return free_ >= n; });
     free_ -= n;
 }
 
 bool TeamSlots::try_acquire(int n) {
+    SHELL_CHECK(n <= capacity_, SHELL_E_UNSUPPORTED, "a team with more members than the device has compute units");
     std::lock_guard<std::mutex> lk(m_);
     if (free_ < n) return false;
     free_ -= n;
@@ -482,7 +481,7 @@ std::vector<const TeamPart*> team_parts(const shell_batch_s& b, int pcg_workgrou
         int64_t members = 0;
         for (const shell_sim_s* sim : b.sims) {
             const TeamPart* own = team_part(*sim->h, 0, s);
-            if (!own) return parts;
+            if (!own || own->members > cus) return parts;
             members += rows > own->rows ? (sim->nv + rows - 1) / rows : own->members;
         }
         if (b.sims.size() > 1 && members > cus && rows < 2048) continue;

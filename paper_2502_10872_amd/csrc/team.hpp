@@ -32,6 +32,7 @@
 
 #include "devmath.hpp"
 #include "internal.hpp"
+#include "team_host.hpp"
 
 namespace shell {
 

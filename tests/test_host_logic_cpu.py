@@ -17,3 +17,7 @@ def run_host(tmp_path, name, *args):
 
 def test_arrival_counters_return_to_zero(tmp_path):
     run_host(tmp_path, "arrivals")
+
+
+def test_a_team_never_has_more_members_than_compute_units(tmp_path):
+    run_host(tmp_path, "team_rows")
