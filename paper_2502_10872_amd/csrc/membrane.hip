@@ -1619,7 +1619,7 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
         bool solved = false;
         if (m.tpart && p.pcg_workgroups == 0) {
             const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
-            TeamSlots& cu = TeamSlots::of_current_device();
+            TeamSlots& cu = team_slots();
             for (bool resume = false; !solved; resume = true) {
                 TeamLease lease;
                 while (!lease.try_take(cu, m.tpart->members)) co_await Later{};
@@ -1744,8 +1744,8 @@ shell_status_t membrane_batch_step(shell_batch_s& b, const shell_step_params_t* 
         } start_guard{start};
         SHELL_HIP(hipEventRecord(start, s));
         for (hipStream_t l : lanes) SHELL_HIP(hipStreamWaitEvent(l, start, 0));
+        std::vector<StepTask> tasks;  // outlive the drain: they hold the compute units of what still runs
         LaneDrain drain{lanes};
-        std::vector<StepTask> tasks;
         tasks.reserve(n);
         for (size_t i = 0; i < n; ++i)
             tasks.push_back(membrane_step_task(*b.sims[i], p[nparams == 1 ? 0 : i], out[i], lanes[i]));
@@ -1830,7 +1830,7 @@ shell_status_t membrane_static(shell_sim_s& sim, const shell_step_params_t& p, c
         if (m.tpart && p.pcg_workgroups == 0) {
             const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
             for (bool resume = false; !solved; resume = true) {
-                TeamLease lease(TeamSlots::of_current_device(), m.tpart->members);
+                TeamLease lease(team_slots(), m.tpart->members);
                 launch_team(sim, sim.zmass.p, 1.0, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
                 read_scal();
                 if (team_gone(hs)) break;
@@ -1909,7 +1909,7 @@ void membrane_time_kernels(shell_sim_s& sim, double dt, int reps, shell_kernel_t
         SHELL_HIP(hipMemcpyAsync(sim.g.p, m.ftry.p, size_t(n3) * sizeof(double), hipMemcpyDeviceToDevice, s));
         double hs[S_COUNT];
         {
-            TeamLease lease(TeamSlots::of_current_device(), m.tpart->members);
+            TeamLease lease(team_slots(), m.tpart->members);
             launch_team(sim, sim.mass.p, dt2, 0.0, reps + 1, true, false, 1 << 30, 1, s);
             SHELL_HIP(hipMemcpyAsync(hs, m.scal.p, sizeof(hs), hipMemcpyDeviceToHost, s));
             SHELL_HIP(hipStreamSynchronize(s));

@@ -75,43 +75,16 @@ GraphCache::~GraphCache() {
     if (capture) (void)hipStreamDestroy(capture);
 }
 
-void TeamSlots::ensure() {
-    if (capacity_) return;
-    capacity_ = free_ = compute_units();
-}
-
-TeamSlots& TeamSlots::of_current_device() {
+TeamSlots& team_slots() {
     constexpr int kMaxDevices = 64;
-    static TeamSlots slots[kMaxDevices];
+    static std::unique_ptr<TeamSlots> slots[kMaxDevices];
+    static std::mutex made;
     int dev = 0;
     SHELL_HIP(hipGetDevice(&dev));
     SHELL_CHECK(dev >= 0 && dev < kMaxDevices, SHELL_E_UNSUPPORTED, "device ordinal beyond the admission table");
-    std::lock_guard<std::mutex> lk(slots[dev].m_);
-    slots[dev].ensure();
-    return slots[dev];
-}
-
-void TeamSlots::acquire(int n) {
-    SHELL_CHECK(n <= capacity_, SHELL_E_UNSUPPORTED, "a team with more members than the device has compute units");
-    std::unique_lock<std::mutex> lk(m_);
-    cv_.wait(lk, [&] { return free_ >= n; });
-    free_ -= n;
-}
-
-bool TeamSlots::try_acquire(int n) {
-    SHELL_CHECK(n <= capacity_, SHELL_E_UNSUPPORTED, "a team with more members than the device has compute units");
-    std::lock_guard<std::mutex> lk(m_);
-    if (free_ < n) return false;
-    free_ -= n;
-    return true;
-}
-
-void TeamSlots::release(int n) {
-    {
-        std::lock_guard<std::mutex> lk(m_);
-        free_ += n;
-    }
-    cv_.notify_all();
+    std::lock_guard<std::mutex> lk(made);
+    if (!slots[dev]) slots[dev] = std::make_unique<TeamSlots>(compute_units());
+    return *slots[dev];
 }
 
 StepProfiler::~StepProfiler() {
@@ -476,7 +449,7 @@ void launch_team(const Launch& L, const WorkItem* items, int members, int rows, 
 std::vector<const TeamPart*> team_parts(const shell_batch_s& b, int pcg_workgroups, hipStream_t s) {
     std::vector<const TeamPart*> parts;
     if (pcg_workgroups > 0 || (b.sims.size() > 1 && b.precision == SHELL_PREC_FP64)) return parts;
-    const int cus = TeamSlots::of_current_device().capacity();
+    const int cus = team_slots().capacity();
     for (int64_t rows : {0, 512, 1024, 1536, 2048}) {
         int64_t members = 0;
         for (const shell_sim_s* sim : b.sims) {
@@ -526,7 +499,7 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         int members = 0, rows = 0;
         size_t lds = 0;
     };
-    const int capacity = teams ? TeamSlots::of_current_device().capacity() : 0;
+    const int capacity = teams ? team_slots().capacity() : 0;
     ItemBuilder ib;
     Launch L;
     std::vector<Group> groups;
@@ -668,7 +641,7 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         // one launch (more when a solve is longer than a launch may be).  False when a member gave up
         // waiting: the solve is then to be run again as a chain.
         auto team_pcg = [&](const std::vector<int>& set, bool refine) -> bool {
-            TeamSlots& cu = TeamSlots::of_current_device();
+            TeamSlots& cu = team_slots();
             std::vector<int> left = set;
             int limit = kTeamChunk, mode = refine ? kTeamRefine : kTeamFresh;
             for (int m : set)
@@ -908,7 +881,7 @@ void time_impl(shell_batch_s& b, double dt, int reps, shell_kernel_times_t& out,
         L = upload(b, ib, s);
         k_team_clear<<<1, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
         {
-            TeamLease lease(TeamSlots::of_current_device(), tp->members);
+            TeamLease lease(team_slots(), tp->members);
             launch_team<VR, MR>(L, L.team, tp->members, tp->rows, team_lds<VR>(tp->rows, tp->max_halo), kTeamFresh,
                                 1 << 30, 1, kTeamWaitTicks, s);
             read_states(b, s);

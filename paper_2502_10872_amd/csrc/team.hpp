@@ -27,9 +27,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <condition_variable>
-#include <mutex>
-
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "team_host.hpp"
@@ -242,41 +239,7 @@ __device__ __forceinline__ V here(V v) {
     return v;
 }
 
-// ------------------------------------------------------------------ admission (host)
-
-// Compute units free for resident teams on one device, one member per unit.  A launch takes its members'
-// units before it is enqueued and gives them back once the host has seen it end.
-class TeamSlots {
-  public:
-    static TeamSlots& of_current_device();
-    int capacity() const { return capacity_; }
-    void acquire(int n);
-    bool try_acquire(int n);
-    void release(int n);
-
-  private:
-    void ensure();
-    std::mutex m_;
-    std::condition_variable cv_;
-    int capacity_ = 0, free_ = 0;
-};
-
-struct TeamLease {
-    TeamSlots* slots = nullptr;
-    int n = 0;
-    TeamLease() = default;
-    TeamLease(TeamSlots& s, int count) : slots(&s), n(count) { s.acquire(count); }
-    bool try_take(TeamSlots& s, int count) {
-        if (!s.try_acquire(count)) return false;
-        slots = &s;
-        n = count;
-        return true;
-    }
-    TeamLease(const TeamLease&) = delete;
-    TeamLease& operator=(const TeamLease&) = delete;
-    ~TeamLease() {
-        if (slots && n) slots->release(n);
-    }
-};
+// compute units for teams on the current device (host)
+TeamSlots& team_slots();
 
 }  // namespace shell

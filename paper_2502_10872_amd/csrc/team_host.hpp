@@ -2,7 +2,11 @@
 #pragma once
 
 #include <algorithm>
+#include <condition_variable>
 #include <cstdint>
+#include <deque>
+#include <mutex>
+#include <stdexcept>
 
 namespace shell {
 
@@ -28,5 +32,83 @@ inline int64_t team_rows(int64_t nv, int cus) {
 // (an iteration reads four times the matrix of the bending solve, so the rows are dealt out sooner: 65536 rows 15.6
 // us with 256, 16.2 with 512; 128 rows gain 8% at 1089 and lose 10% at 16384).
 inline int64_t team_rows_membrane(int64_t nv, int cus) { return team_rows_spread(nv, cus, 512, 256); }
+
+// Compute units free for resident teams on one device, one member per unit.  A launch takes its members'
+// units before it is enqueued and gives them back once the host has seen it end.  Requests are served in the order in
+// which they came: none passes one that waits for more units, so that a mesh which needs all of them gets them once the
+// launches that were in flight when it asked have ended.
+class TeamSlots {
+  public:
+    TeamSlots() = default;
+    explicit TeamSlots(int capacity) : capacity_(capacity), free_(capacity) {}
+    int capacity() const { return capacity_; }
+
+  private:
+    friend struct TeamLease;
+    struct Request {
+        int n;
+    };
+    bool ready(const Request* r) const { return line_.front() == r && free_ >= r->n; }
+    void grant(const Request* r) {
+        line_.pop_front();
+        free_ -= r->n;
+    }
+
+    mutable std::mutex m_;
+    std::condition_variable cv_;
+    std::deque<const Request*> line_;  // requests that wait, the first to be served in front
+    int capacity_ = 0, free_ = 0;
+};
+
+// The units of one launch, or a place in the line for them; both end with it.
+struct TeamLease {
+    TeamLease() = default;
+    // waits until the units are there
+    TeamLease(TeamSlots& s, int n) {
+        std::unique_lock<std::mutex> lk(s.m_);
+        enter(s, n);
+        s.cv_.wait(lk, [&] { return s.ready(&request_); });
+        s.grant(&request_);
+        held_ = true;
+        lk.unlock();
+        s.cv_.notify_all();  // what is left may do for the next
+    }
+    // true once the units are there; until then the request keeps its place in the line.  The caller asks again.
+    bool try_take(TeamSlots& s, int n) {
+        std::lock_guard<std::mutex> lk(s.m_);
+        if (!slots_) enter(s, n);
+        if (!held_ && s.ready(&request_)) {
+            s.grant(&request_);
+            held_ = true;
+            s.cv_.notify_all();
+        }
+        return held_;
+    }
+    TeamLease(const TeamLease&) = delete;
+    TeamLease& operator=(const TeamLease&) = delete;
+    ~TeamLease() {
+        if (!slots_) return;
+        {
+            std::lock_guard<std::mutex> lk(slots_->m_);
+            auto& line = slots_->line_;
+            if (held_)
+                slots_->free_ += request_.n;
+            else
+                line.erase(std::find(line.begin(), line.end(), &request_));
+        }
+        slots_->cv_.notify_all();
+    }
+
+  private:
+    void enter(TeamSlots& s, int n) {
+        if (n > s.capacity_) throw std::length_error("a team with more members than the device has compute units");
+        s.line_.push_back(&request_);
+        slots_ = &s;
+        request_.n = n;
+    }
+    TeamSlots* slots_ = nullptr;
+    TeamSlots::Request request_{0};
+    bool held_ = false;
+};
 
 }  // namespace shell

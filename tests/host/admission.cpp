@@ -1,0 +1,74 @@
+// Admission of teams: requests in the order in which they came, from one thread that polls and from several that wait.
+#include <atomic>
+#include <chrono>
+#include <cstdio>
+#include <cstdlib>
+#include <memory>
+#include <thread>
+#include <vector>
+
+#include "team_host.hpp"
+
+using namespace shell;
+
+static void check(bool ok, const char* what) {
+    if (ok) return;
+    std::printf("%s\n", what);
+    std::exit(1);
+}
+
+static void polled() {
+    TeamSlots s(256);
+    auto a = std::make_unique<TeamLease>(), b = std::make_unique<TeamLease>(), all = std::make_unique<TeamLease>(),
+         gone = std::make_unique<TeamLease>(), c = std::make_unique<TeamLease>();
+    check(a->try_take(s, 100) && b->try_take(s, 100), "two leases that fit");
+    check(!all->try_take(s, 256), "a request for all waits");
+    a.reset();
+    check(!gone->try_take(s, 8) && !c->try_take(s, 100), "nothing passes the request for all");
+    b.reset();
+    check(!c->try_take(s, 100), "nothing passes it when it could be served, either");
+    check(all->try_take(s, 256) && all->try_take(s, 256), "the request for all is served, and stays so");
+    all.reset();
+    check(!c->try_take(s, 100), "its turn comes after the one before");
+    gone.reset();  // a request that is given up leaves the line
+    check(c->try_take(s, 100), "then its own");
+    c.reset();
+    bool refused = false;
+    try {
+        TeamLease over(s, 257);
+    } catch (const std::length_error&) {
+        refused = true;
+    }
+    check(refused, "more than there are");
+    TeamLease again(s, 256);
+}
+
+static void threads() {
+    TeamSlots s(256);
+    std::atomic<int> in_use{0};
+    std::atomic<bool> stop{false};
+    auto worker = [&](int n, bool poll) {
+        while (!stop) {
+            auto lease = poll ? std::make_unique<TeamLease>() : std::make_unique<TeamLease>(s, n);
+            while (poll && !lease->try_take(s, n)) std::this_thread::yield();
+            check((in_use += n) <= 256, "more units than there are");
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
+            in_use -= n;
+        }
+    };
+    std::vector<std::thread> small;
+    for (int k = 0; k < 4; ++k) small.emplace_back(worker, 64 + 16 * k, k % 2 == 1);
+    for (int k = 0; k < 100; ++k) {
+        TeamLease all(s, 256);
+        check((in_use += 256) == 256, "all units");
+        in_use -= 256;
+    }
+    stop = true;
+    for (auto& t : small) t.join();
+}
+
+int main() {
+    polled();
+    threads();
+    std::puts("ok");
+}

@@ -8,6 +8,7 @@ rounding's growth small: FP64 agrees to 1e-10 (the oracle parity bound), mixed p
 the full-size mixed iteration against the oracle)."""
 
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -251,3 +252,57 @@ def test_membrane_solves_of_one_member_equal_the_kernel_chain_and_the_direct_pro
     for wg, flags in ((512, 0), (0, S.SHELL_FLAG_DIRECT_PRODUCT)):
         xb, vb = _membrane_run(mesh, x, v, precision, wg=wg, flags=flags, held=held)
         assert rel(xa - mesh.X, xb - mesh.X) <= bound and rel(va, vb) <= bound
+
+
+def _steps_of(kind, torch, out, errors):
+    """Three steps of one user on a stream of its own: a mesh whose team takes nearly all compute units, a small mesh,
+    a mixed-precision batch, a batch with the membrane."""
+    try:
+        flags = S.SHELL_FLAG_MEMBRANE if kind == "membrane" else 0
+        precision = S.SHELL_PREC_MIXED if kind == "batch" else S.SHELL_PREC_FP64
+        meshes = {"large": [I.workload_sphere_cap(400, "SS")], "small": [I.workload_cylinder(70, "FS")],
+                  "batch": [I.workload_cylinder(60, "SS"), I.workload_sphere_cap(130, "ES")],
+                  "membrane": [I.workload_cylinder(n, "SS") for n in (40, 20, 90)]}[kind]
+        probs = [S.Problem(m, MAT, precision=precision, flags=flags) for m in meshes]
+        batch = None
+        try:
+            for pb, m in zip(probs, meshes):
+                S.shell_sim_set_state(pb.sim, *_start(m), 0)
+            stream = torch.cuda.Stream()
+            params, _keep = S.step_params(1 / 60, max_newton=2, newton_rtol=0.0, pcg_rtol=1e-4, max_pcg=400)
+            if len(probs) > 1:
+                batch = S.shell_batch_create([pb.sim for pb in probs])
+            for _ in range(3):
+                if batch is not None:
+                    S.shell_batch_step(batch, params, len(probs), stream=stream)
+                else:
+                    S.shell_step_implicit(probs[0].sim, params, stream=stream)
+            out[kind] = [S.shell_sim_get_state(pb.sim, pb.nv)[:2] for pb in probs]
+        finally:
+            if batch is not None:
+                S.shell_destroy_batch(batch)
+            for pb in probs:
+                pb.close()
+    except BaseException as e:  # reported by the main thread
+        errors.append((kind, e))
+
+
+def test_teams_of_several_threads_reach_what_each_reaches_alone():
+    """Teams share the device's compute units: each launch waits for its members' units, in the order of the requests.
+    Four threads at a time, a mesh that needs nearly all units among them, reach their own results bit for bit."""
+    kinds = ("large", "small", "batch", "membrane")
+    alone, errors = {}, []
+    for kind in kinds:
+        _steps_of(kind, torch, alone, errors)
+    assert not errors, errors
+    together = {}
+    threads = [threading.Thread(target=_steps_of, args=(kind, torch, together, errors)) for kind in kinds]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=100)
+    assert not any(t.is_alive() for t in threads)
+    assert not errors, errors
+    for kind in kinds:
+        for (xa, va), (xt, vt) in zip(alone[kind], together[kind]):
+            assert np.isfinite(xa).all() and np.array_equal(xa, xt) and np.array_equal(va, vt), kind
