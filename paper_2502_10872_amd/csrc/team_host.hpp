@@ -33,8 +33,13 @@ inline int64_t team_rows(int64_t nv, int cus) {
 // us with 256, 16.2 with 512; 128 rows gain 8% at 1089 and lose 10% at 16384).
 inline int64_t team_rows_membrane(int64_t nv, int cus) { return team_rows_spread(nv, cus, 512, 256); }
 
+constexpr int kCusPerXcd = 32;  // compute units that an XCD of the MI355X has in use
+
 // Compute units free for resident teams on one device, one member per unit.  A launch takes its members'
-// units before it is enqueued and gives them back once the host has seen it end.  Requests are served in the order in
+// units before it is enqueued and gives them back once the host has seen it end.  The device deals a launch's
+// work-groups round-robin over its XCDs, so a team of n members may bring any XCD ceil(n / XCDs) of them, and it takes that
+// many units of each: with n alone counted, teams of 66, 66, 66 and 58 members (256) would bring the first XCD 35 for
+// its 32 units, and each of them might hold back one member that the others' wait for.  Requests are served in the order in
 // which they came: none passes one that waits for more units, so that a mesh which needs all of them gets them once the
 // launches that were in flight when it asked have ended.
 class TeamSlots {
@@ -42,6 +47,11 @@ class TeamSlots {
     TeamSlots() = default;
     explicit TeamSlots(int capacity) : capacity_(capacity), free_(capacity) {}
     int capacity() const { return capacity_; }
+    // units a team of n members takes
+    int units(int n) const {
+        const int xcds = std::max(1, capacity_ / kCusPerXcd);
+        return std::min(capacity_, (n + xcds - 1) / xcds * xcds);
+    }
 
   private:
     friend struct TeamLease;
@@ -104,7 +114,7 @@ struct TeamLease {
         if (n > s.capacity_) throw std::length_error("a team with more members than the device has compute units");
         s.line_.push_back(&request_);
         slots_ = &s;
-        request_.n = n;
+        request_.n = s.units(n);
     }
     TeamSlots* slots_ = nullptr;
     TeamSlots::Request request_{0};

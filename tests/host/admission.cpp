@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <memory>
+#include <random>
 #include <thread>
 #include <vector>
 
@@ -43,6 +44,29 @@ static void polled() {
     TeamLease again(s, 256);
 }
 
+// Whatever teams are in flight together, no XCD has more of their members than units.
+static void xcds() {
+    std::mt19937 rng(1);
+    for (int cus : {32, 64, 256})
+        for (int trial = 0; trial < 2000; ++trial) {
+            TeamSlots s(cus);
+            std::vector<std::unique_ptr<TeamLease>> held;
+            std::vector<int> load(size_t(cus / kCusPerXcd), 0);
+            for (int k = 0; k < 12; ++k) {
+                const int n = 1 + int(rng() % (k % 2 ? 20u : unsigned(cus)));
+                held.push_back(std::make_unique<TeamLease>());
+                if (!held.back()->try_take(s, n)) {
+                    held.pop_back();  // not admitted
+                    continue;
+                }
+                const int first = int(rng() % load.size());
+                for (int m = 0; m < n; ++m) load[size_t(first + m) % load.size()]++;
+            }
+            check(!held.empty(), "a team that fits");
+            for (int l : load) check(l <= kCusPerXcd, "more members on an XCD than units");
+        }
+}
+
 static void threads() {
     TeamSlots s(256);
     std::atomic<int> in_use{0};
@@ -51,9 +75,9 @@ static void threads() {
         while (!stop) {
             auto lease = poll ? std::make_unique<TeamLease>() : std::make_unique<TeamLease>(s, n);
             while (poll && !lease->try_take(s, n)) std::this_thread::yield();
-            check((in_use += n) <= 256, "more units than there are");
+            check((in_use += s.units(n)) <= 256, "more units than there are");
             std::this_thread::sleep_for(std::chrono::microseconds(50));
-            in_use -= n;
+            in_use -= s.units(n);
         }
     };
     std::vector<std::thread> small;
@@ -69,6 +93,7 @@ static void threads() {
 
 int main() {
     polled();
+    xcds();
     threads();
     std::puts("ok");
 }
