@@ -1429,9 +1429,6 @@ static void pcg_iterations(MembraneSolve& m, const double* mass, const uint8_t* 
 
 namespace {
 
-// Iterations of one launch at most (a launch of the largest meshes then takes some 0.5 s).
-constexpr int kMsTeamChunk = 4096;
-
 // One launch of the team solve of (M + dt^2 (K_s (x) I3 + K_m)) y = -g, or its continuation.
 void launch_team(shell_sim_s& sim, const double* mass, double dt2, double rtol2, int target, bool replay, bool resume,
                  int limit, int every, hipStream_t s) {
@@ -1490,6 +1487,12 @@ void launch_team(shell_sim_s& sim, const double* mass, double dt2, double rtol2,
     else if (rpl <= 6) go(ms_team_pcg<double, 6>, ms_team_pcg<float, 6>);
     else go(ms_team_pcg<double, 8>, ms_team_pcg<float, 8>);
     SHELL_HIP(hipGetLastError());
+}
+
+// iterations of the next launch at most
+int launch_iterations(const MembraneSolve& m, int chunk, const TeamSlots& cu) {
+    const int n = team_launch_iterations(m.tpart->rows, true, cu.shared());
+    return chunk > 0 ? std::min(chunk, n) : n;
 }
 
 // whether a member of the last launch gave up waiting, from the fetched scalars
@@ -1618,9 +1621,9 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
         if (m.tpart && p.pcg_workgroups == 0) {
-            const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
             TeamSlots& cu = team_slots();
             for (bool resume = false; !solved; resume = true) {
+                const int limit = launch_iterations(m, p.chunk, cu);
                 TeamLease lease;
                 while (!lease.try_take(cu, m.tpart->members)) co_await Later{};
                 launch_team(sim, sim.mass.p, dt2, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
@@ -1828,9 +1831,10 @@ shell_status_t membrane_static(shell_sim_s& sim, const shell_step_params_t& p, c
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
         if (m.tpart && p.pcg_workgroups == 0) {
-            const int limit = p.chunk > 0 ? std::min(int(p.chunk), kMsTeamChunk) : kMsTeamChunk;
+            TeamSlots& cu = team_slots();
             for (bool resume = false; !solved; resume = true) {
-                TeamLease lease(team_slots(), m.tpart->members);
+                const int limit = launch_iterations(m, p.chunk, cu);
+                TeamLease lease(cu, m.tpart->members);
                 launch_team(sim, sim.zmass.p, 1.0, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
                 read_scal();
                 if (team_gone(hs)) break;

@@ -26,6 +26,7 @@
 // iterations; float64 residual r, all dot products and the Newton residual.
 #include <algorithm>
 #include <cfloat>
+#include <climits>
 #include <cmath>
 #include <cstring>
 
@@ -420,9 +421,6 @@ ForceDesc force_desc(shell_sim_s& sim) {
 
 // ------------------------------------------------------------------ team solves
 
-// Iterations of one launch at most (a launch of the largest meshes then takes some 0.3 s).
-constexpr int kTeamChunk = 8192;
-
 template <typename VR, typename MR>
 void launch_team(const Launch& L, const WorkItem* items, int members, int rows, size_t lds, int mode, int limit,
                  int every, uint64_t wait, hipStream_t s) {
@@ -643,9 +641,9 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         auto team_pcg = [&](const std::vector<int>& set, bool refine) -> bool {
             TeamSlots& cu = team_slots();
             std::vector<int> left = set;
-            int limit = kTeamChunk, mode = refine ? kTeamRefine : kTeamFresh;
+            int chunk = INT_MAX, mode = refine ? kTeamRefine : kTeamFresh;
             for (int m : set)
-                if (ms[size_t(m)].prm->chunk > 0) limit = std::min(limit, int(ms[size_t(m)].prm->chunk));
+                if (ms[size_t(m)].prm->chunk > 0) chunk = std::min(chunk, int(ms[size_t(m)].prm->chunk));
             const int every = b.prof ? b.prof->every : 0;
             set_targets(set, k, refine);
             while (!left.empty()) {
@@ -654,8 +652,12 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
                 if (mode == kTeamRefine) refine_start(left);
                 if (mode != kTeamFresh)  // the residual's kernel has readied a first launch's slots
                     k_team_clear<<<L.nmeshes, kRedBlk, 0, s>>>(L.sdesc, L.meshes);
-                int most = 0;
-                for (const Group& g : groups) most = std::max(most, g.members);
+                int most = 0, rows = 0;
+                for (const Group& g : groups) {
+                    most = std::max(most, g.members);
+                    rows = std::max(rows, g.rows);
+                }
+                const int limit = std::min(chunk, team_launch_iterations(rows, false, cu.shared()));
                 {
                     TeamLease lease(cu, most);
                     for (const Group& g : groups)

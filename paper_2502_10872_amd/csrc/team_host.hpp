@@ -47,6 +47,11 @@ class TeamSlots {
     TeamSlots() = default;
     explicit TeamSlots(int capacity) : capacity_(capacity), free_(capacity) {}
     int capacity() const { return capacity_; }
+    // whether other launches are in flight or in line
+    bool shared() const {
+        std::lock_guard<std::mutex> lk(m_);
+        return free_ != capacity_ || !line_.empty();
+    }
     // units a team of n members takes
     int units(int n) const {
         const int xcds = std::max(1, capacity_ / kCusPerXcd);
@@ -69,6 +74,16 @@ class TeamSlots {
     std::deque<const Request*> line_;  // requests that wait, the first to be served in front
     int capacity_ = 0, free_ = 0;
 };
+
+// Iterations of one launch at most.  A launch keeps its units until it ends, which other work waits for (a chain of
+// kernels lets it in at every kernel), so it takes some 50 ms, or 10 ms where other teams want units too; a longer solve
+// goes on in another launch, on the same bits (1M rows, 8000 iterations: 337.6 -> 338.2 ms FP64 and 247.8 -> 249.5 mixed
+// against one launch).  An iteration takes about
+// 8 us and 1 us per 120 rows of a member (42 us at 4096 rows FP64), with the membrane 9 us and 1 us per 36 (122 us).
+inline int team_launch_iterations(int64_t rows, bool membrane, bool shared) {
+    const double us = membrane ? 9.0 + double(rows) / 36 : 8.0 + double(rows) / 120;
+    return int((shared ? 10e3 : 50e3) / us);
+}
 
 // The units of one launch, or a place in the line for them; both end with it.
 struct TeamLease {

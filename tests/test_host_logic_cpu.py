@@ -25,3 +25,7 @@ def test_a_team_never_has_more_members_than_compute_units(tmp_path):
 
 def test_teams_are_admitted_in_the_order_of_their_requests(tmp_path):
     run_host(tmp_path, "admission")
+
+
+def test_launches_of_a_team_are_short_and_shorter_where_others_wait(tmp_path):
+    run_host(tmp_path, "launch_length")
