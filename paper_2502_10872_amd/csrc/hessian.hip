@@ -10,7 +10,6 @@
 #include "devmath.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
-#include "team_host.hpp"
 
 namespace shell {
 

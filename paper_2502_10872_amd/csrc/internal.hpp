@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "shell.h"
+#include "team_host.hpp"
 
 namespace shell {
 
@@ -438,6 +439,7 @@ struct MembraneSolve {
     // the stream the simulation steps on inside a batch
     double* hscal = nullptr;
     uint64_t team_wait = ~uint64_t(0);  // ticks a team's wait may take (tests shorten it)
+    shell::TeamRecord teams;
     hipEvent_t ready = nullptr;
     hipStream_t lane = nullptr;
     // device memory held by the arrays above
@@ -553,6 +555,7 @@ struct shell_batch_s {
     shell::DevArray<shell::WorkItem> items;   // [rows | tiles of each model]
     bool membrane = false;  // simulations with the membrane: the members' steps interleave on their own streams
     uint64_t team_wait = ~uint64_t(0);  // ticks a team's wait may take (tests shorten it)
+    shell::TeamRecord teams;
 };
 
 namespace shell {

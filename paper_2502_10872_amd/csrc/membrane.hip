@@ -1620,7 +1620,7 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
         // (no team, the chain asked for by its work-groups, or a member gave up waiting) as a chain of kernels
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
-        if (m.tpart && p.pcg_workgroups == 0) {
+        if (m.tpart && p.pcg_workgroups == 0 && !m.teams.rests()) {
             TeamSlots& cu = team_slots();
             for (bool resume = false; !solved; resume = true) {
                 const int limit = launch_iterations(m, p.chunk, cu);
@@ -1628,9 +1628,13 @@ StepTask membrane_step_task(shell_sim_s& sim, shell_step_params_t p, shell_step_
                 while (!lease.try_take(cu, m.tpart->members)) co_await Later{};
                 launch_team(sim, sim.mass.p, dt2, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
                 co_await fetch();
-                if (team_gone(hs)) break;
+                if (team_gone(hs)) {
+                    m.teams.gave_up();
+                    break;
+                }
                 solved = pcg()[S_ACTIVE] == 0.0;
             }
+            if (solved) m.teams.met();
         }
         if (!solved) {
             m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction
@@ -1830,16 +1834,20 @@ shell_status_t membrane_static(shell_sim_s& sim, const shell_step_params_t& p, c
         tangent_at(sim, sim.x.p, sim.zmass.p, 1.0, s);
         const int target = replay ? p.replay_counts[3 * k] : p.max_pcg;
         bool solved = false;
-        if (m.tpart && p.pcg_workgroups == 0) {
+        if (m.tpart && p.pcg_workgroups == 0 && !m.teams.rests()) {
             TeamSlots& cu = team_slots();
             for (bool resume = false; !solved; resume = true) {
                 const int limit = launch_iterations(m, p.chunk, cu);
                 TeamLease lease(cu, m.tpart->members);
                 launch_team(sim, sim.zmass.p, 1.0, p.pcg_rtol * p.pcg_rtol, target, replay, resume, limit, 0, s);
                 read_scal();
-                if (team_gone(hs)) break;
+                if (team_gone(hs)) {
+                    m.teams.gave_up();
+                    break;
+                }
                 solved = pcg()[S_ACTIVE] == 0.0;
             }
+            if (solved) m.teams.met();
         }
         if (!solved) {
             m.pswap = false;  // ms_pcg_init writes p = z into m.p, the first product's old direction

@@ -687,7 +687,13 @@ shell_status_t step_impl(shell_batch_s& b, const shell_step_params_t* prms, int 
         // first kernel (from r = -g, or for a refinement pass from the true residual of the increment so
         // far), the first product, then chunks until every mesh is done.  Returns the last product launched.
         auto run_pcg = [&](const std::vector<int>& set, bool refine) -> long {
-            if (teams && team_pcg(set, refine)) return 0;
+            if (teams && !b.teams.rests()) {
+                if (team_pcg(set, refine)) {
+                    b.teams.met();
+                    return 0;
+                }
+                b.teams.gave_up();
+            }
             list_items(set);
             set_targets(set, k, refine);
             set_slot_ranges(b, L, ib);

@@ -20,23 +20,24 @@
 // plate (9 to 17 members): 2 us from a member's first store to every member's total.
 //
 // Every wait is bounded: past the launch's limit a member gives up, raises the team's flag and leaves, as
-// every other member then does; the host finds the flag and runs the solve as a chain of kernels.  That
-// can only happen when other work keeps some members from ever becoming resident.  Within a process the
-// host admits a launch only while compute units are left for all of its members (TeamSlots).
+// every other member then does; the host finds the flag and runs the solve, and the next few (TeamRecord), as a
+// chain of kernels.  That can only happen when other work keeps some members from becoming resident.  Within a
+// process the host admits a launch only while compute units are left for all of its members (TeamSlots).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "devmath.hpp"
 #include "internal.hpp"
-#include "team_host.hpp"
 
 namespace shell {
 
 constexpr unsigned long long kUnset = 0x7ff8dead0000beefull;
 constexpr unsigned long long kPlainNan = 0x7ff8000000000000ull;
 constexpr int kTeamQ = 6;                    // sums per exchange at most
-constexpr uint64_t kTeamWaitTicks = 200000000;  // 2 s of the 100 MHz wall clock: the longest wait
+// The longest wait: 100 ms of the 100 MHz wall clock, 800 iterations of the largest meshes (a member once resident waits
+// for part of one).
+constexpr uint64_t kTeamWaitTicks = 10000000;
 
 // slots of one mesh: [set][parity][sum][member], then the flag
 __host__ __device__ constexpr size_t team_slot_count(int members) { return size_t(2 * 2 * kTeamQ) * size_t(members); }

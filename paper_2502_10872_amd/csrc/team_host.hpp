@@ -85,6 +85,19 @@ inline int team_launch_iterations(int64_t rows, bool membrane, bool shared) {
     return int((shared ? 10e3 : 50e3) / us);
 }
 
+// What a handle knows of how its teams fare.  Members that cannot all become resident (another process's team
+// dispatched at the same time, a stream with fewer compute units) wait for kTeamWaitTicks and hand the solve to the chain
+// of kernels; the next 16 solves then take the chain at once, twice as many after each further failure, up to 1024.
+struct TeamRecord {
+    // once per solve: whether it is to take the chain
+    bool rests() { return rest_ > 0 && rest_-- > 0; }
+    void gave_up() { rest_ = last_ = std::min(1024, std::max(16, 2 * last_)); }
+    void met() { last_ = 0; }
+
+  private:
+    int rest_ = 0, last_ = 0;
+};
+
 // The units of one launch, or a place in the line for them; both end with it.
 struct TeamLease {
     TeamLease() = default;

@@ -306,3 +306,23 @@ def test_teams_of_several_threads_reach_what_each_reaches_alone():
     for kind in kinds:
         for (xa, va), (xt, vt) in zip(alone[kind], together[kind]):
             assert np.isfinite(xa).all() and np.array_equal(xa, xt) and np.array_equal(va, vt), kind
+
+
+@pytest.mark.parametrize("flags", [0, S.SHELL_FLAG_MEMBRANE])
+def test_solves_after_one_that_gave_up_take_the_chain_at_once(flags):
+    """Two solves a step: the one that gives up and the 16 after it run as the chain, whatever the wait allowed, and
+    then teams again."""
+    mesh = I.workload_cylinder(100, "SS")
+    x, v = _start(mesh)
+    n = [20, 0, 0] if flags else 20  # with the membrane: iterations, halvings
+    with S.Problem(mesh, MAT, flags=flags) as pb:
+        team = _step(pb, mesh, x, v, iters=n)[:2]
+        chain = _step(pb, mesh, x, v, wg=512, iters=n)[:2]
+        assert not np.array_equal(team[1], chain[1])
+        _no_waiting(pb.sim, 0)
+        ends = [_step(pb, mesh, x, v, iters=n)[:2]]
+        _no_waiting(pb.sim, 2 ** 64 - 1)
+        ends += [_step(pb, mesh, x, v, iters=n)[:2] for _ in range(9)]
+    for end in ends[:8]:  # 16 of 17 solves
+        assert np.array_equal(end[0], chain[0]) and np.array_equal(end[1], chain[1])
+    assert np.array_equal(ends[9][0], team[0]) and np.array_equal(ends[9][1], team[1])

@@ -29,3 +29,7 @@ def test_teams_are_admitted_in_the_order_of_their_requests(tmp_path):
 
 def test_launches_of_a_team_are_short_and_shorter_where_others_wait(tmp_path):
     run_host(tmp_path, "launch_length")
+
+
+def test_how_long_solves_keep_to_the_chain(tmp_path):
+    run_host(tmp_path, "team_record")
