@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "devmath.hpp"
+#include "host_threads.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
 

@@ -4,8 +4,8 @@
 #include <algorithm>
 #include <cstring>
 #include <numeric>
-#include <thread>
 
+#include "host_threads.hpp"
 #include "internal.hpp"
 
 namespace shell {
@@ -16,33 +16,10 @@ inline uint64_t dkey(int32_t from, int32_t to) { return (uint64_t(uint32_t(from)
 
 template <typename F>
 void parallel_for(int64_t n, F&& fn) {
-    unsigned nt = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    if (n < 4096 || nt == 1) {
-        fn(int64_t(0), n);
-        return;
-    }
-    std::vector<std::thread> th;
-    int64_t chunk = (n + nt - 1) / nt;
-    for (unsigned t = 0; t < nt; ++t) {
-        int64_t a = t * chunk, b = std::min(n, a + chunk);
-        if (a < b) th.emplace_back([=, &fn] { fn(a, b); });
-    }
-    for (auto& t : th) t.join();
+    host_parallel_for(n, fn, 4096);
 }
 
 }  // namespace
-
-void host_parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn, int64_t small) {
-    const int64_t nt = std::max<int64_t>(1, std::min<int64_t>({16, int64_t(std::thread::hardware_concurrency()), n}));
-    if (n < small || nt == 1) {
-        if (n > 0) fn(0, n);
-        return;
-    }
-    std::vector<std::thread> th;
-    const int64_t chunk = (n + nt - 1) / nt;
-    for (int64_t a = 0; a < n; a += chunk) th.emplace_back([=, &fn] { fn(a, std::min(n, a + chunk)); });
-    for (auto& t : th) t.join();
-}
 
 HostTopology build_topology(int model, int64_t nv, int64_t nt, const int32_t* tris, int64_t n_clamped,
                             const int32_t* clamped) {

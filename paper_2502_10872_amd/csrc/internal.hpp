@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <functional>
 #include <stdexcept>
 #include <string>
 #include <memory>
@@ -182,8 +181,6 @@ struct SellPattern {
 };
 constexpr int kRowGroup = 512;     // rows per work item (and threads per work-group) of the row kernels
 constexpr int kMaxGroupCols = 4096;  // largest column set staged in LDS (larger: direct gathers)
-// runs fn(first, last) over [0, n) on the host's threads; ranges in chunks, n below `small` on this thread
-void host_parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn, int64_t small = 1);
 // team solves (team.hpp): most rows of a member, and the LDS for its directions (two kilobytes short of a CU's)
 constexpr int kTeamMaxRows = 4096;
 constexpr size_t kTeamLds = 158 * 1024;

@@ -33,3 +33,7 @@ def test_launches_of_a_team_are_short_and_shorter_where_others_wait(tmp_path):
 
 def test_how_long_solves_keep_to_the_chain(tmp_path):
     run_host(tmp_path, "team_record")
+
+
+def test_what_a_host_thread_throws_reaches_the_caller(tmp_path):
+    run_host(tmp_path, "host_threads")
