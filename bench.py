@@ -691,9 +691,22 @@ def serving_run(torch, rates=(20.0, 200.0), durations=(3.0, 1.0), max_wait_s=5.0
     return out
 
 
-def timed_steps(S, torch, pb, params, steps, sample_every, label):
-    """`steps` implicit steps on the library's stream; wall time bracketed by stream synchronisation and
-    kernel durations sampled in-step with HIP events (see shell_sim_profile)."""
+# Steps of one trajectory from rest.  The headline's shell has bending stiffness alone: gravity stretches it in plane
+# without resistance, triangles reach 1e7 times their rest area after 10 steps, and the next step is refused as non-finite
+# after 13 of them (FP64) or 17 (mixed); which one depends on rounding.
+TRAJECTORY_STEPS = 8
+
+
+def starts_again(step: int) -> bool:
+    """Whether the simulation goes back to rest before its `step`-th step (warm-up steps count)."""
+    return step > 0 and step % TRAJECTORY_STEPS == 0
+
+
+def timed_steps(S, torch, pb, params, steps, sample_every, label, first=0):
+    """`steps` implicit steps on the library's stream, the first of them the simulation's `first`-th; wall time
+    bracketed by stream synchronisation (the returns to rest are inside it) and kernel durations sampled in-step with
+    HIP events (see shell_sim_profile)."""
+    rest, still = pb.mesh.X, np.zeros_like(pb.mesh.X)
     stream = torch.cuda.current_stream()
     torch.cuda.synchronize()
     S.shell_sim_profile(pb.sim, sample_every)
@@ -701,6 +714,8 @@ def timed_steps(S, torch, pb, params, steps, sample_every, label):
     t_start = time.perf_counter()
     for k in range(steps):
         t0 = time.perf_counter()
+        if starts_again(first + k):
+            S.shell_sim_set_state(pb.sim, rest, still, 0)
         rc, st = S.shell_step_implicit(pb.sim, params, stream=stream)
         torch.cuda.synchronize()
         lat.append(time.perf_counter() - t0)
@@ -927,15 +942,18 @@ def main(argv=None):
     for w in range(args.warmup):
         for q in (pb, pb_other):
             if q is not None:
+                if starts_again(w):
+                    S.shell_sim_set_state(q.sim, mesh.X, np.zeros_like(mesh.X), 0)
                 rc, st = S.shell_step_implicit(q.sim, params)
                 print(f"[bench] warmup {w}: newton {st['newton_iters']} pcg {st['pcg_total']}", file=sys.stderr,
                       flush=True)
-    elapsed, stats, lat, prof = timed_steps(S, torch, pb, params, args.steps, args.sample_every, args.precision)
+    elapsed, stats, lat, prof = timed_steps(S, torch, pb, params, args.steps, args.sample_every, args.precision,
+                                           first=args.warmup)
     steps_per_s = args.steps / elapsed
     compare = None
     if pb_other is not None:
         e2, st2, lat2, prof2 = timed_steps(S, torch, pb_other, params, args.steps, args.sample_every,
-                                           "fp64" if other == S.SHELL_PREC_FP64 else "mixed")
+                                           "fp64" if other == S.SHELL_PREC_FP64 else "mixed", first=args.warmup)
         pb64, pbm = (pb_other, pb) if head == S.SHELL_PREC_MIXED else (pb, pb_other)
         ferr = force_error(S, torch, mesh, pb64, pbm)
         errs = step_error(S, torch, mesh, pb64, pbm, params, args.error_steps)
@@ -989,7 +1007,8 @@ def main(argv=None):
         dtype="f64" if head == S.SHELL_PREC_FP64 else "f32+f64", data="synthetic",
         config=dict(workload=f"sphere-cap smoothed-hinge shell (SS), {args.size}x{args.size} vertices, "
                              f"R={mesh.meta['radius']:.4f} m, jitter 0.2, ring pinned, dt=1/30 s, "
-                             f"Newton budget {args.max_newton}, Jacobi-PCG rtol {args.pcg_rtol:g}",
+                             f"Newton budget {args.max_newton}, Jacobi-PCG rtol {args.pcg_rtol:g}, from rest again "
+                             f"every {TRAJECTORY_STEPS} steps",
                     nv=mesh.nv, stencils=pb.info["ns"], nnz=hinfo["nnz"], precision=args.precision,
                     parallelism="single GPU"),
         roofline=dict(bound="hbm", kernel="k_team_pcg (product phase: PCG state, direction update, 3-column product)",
