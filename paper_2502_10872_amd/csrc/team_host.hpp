@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <chrono>
 #include <condition_variable>
 #include <cstdint>
 #include <deque>
@@ -37,15 +38,18 @@ constexpr int kCusPerXcd = 32;  // compute units that an XCD of the MI355X has i
 
 // Compute units free for resident teams on one device, one member per unit.  A launch takes its members'
 // units before it is enqueued and gives them back once the host has seen it end.  The device deals a launch's
-// work-groups round-robin over its XCDs, so a team of n members may bring any XCD ceil(n / XCDs) of them, and it takes that
-// many units of each: with n alone counted, teams of 66, 66, 66 and 58 members (256) would bring the first XCD 35 for
-// its 32 units, and each of them might hold back one member that the others' wait for.  Requests are served in the order in
-// which they came: none passes one that waits for more units, so that a mesh which needs all of them gets them once the
-// launches that were in flight when it asked have ended.
+// work-groups round-robin over its XCDs, so a team of n members may bring any XCD ceil(n / XCDs) of them, and it takes
+// that many units of each: with n alone counted, teams of 66, 66, 66 and 58 members (256) would bring the first XCD 35
+// for its 32 units, and each of them might hold back one member that the others' wait for.
+// Who finds room takes it until the oldest request has waited for its patience, 100 ms; from then on none passes that
+// one, so that a mesh which needs all units gets them once the launches in flight have ended.  In strict order a batch
+// with the membrane of 32 meshes, a fifth of which need all units, drained the device for each of their launches: 375 ms
+// a step, against 349 without order and with this one.
 class TeamSlots {
   public:
     TeamSlots() = default;
-    explicit TeamSlots(int capacity) : capacity_(capacity), free_(capacity) {}
+    explicit TeamSlots(int capacity, std::chrono::microseconds patience = std::chrono::milliseconds(100))
+        : patience_(patience), capacity_(capacity), free_(capacity) {}
     int capacity() const { return capacity_; }
     // whether other launches are in flight or in line
     bool shared() const {
@@ -62,16 +66,22 @@ class TeamSlots {
     friend struct TeamLease;
     struct Request {
         int n;
+        std::chrono::steady_clock::time_point since;
     };
-    bool ready(const Request* r) const { return line_.front() == r && free_ >= r->n; }
+    bool ready(const Request* r) const {
+        const Request* oldest = line_.front();
+        return free_ >= r->n && (r == oldest || std::chrono::steady_clock::now() - oldest->since < patience_);
+    }
+    void leave(const Request* r) { line_.erase(std::find(line_.begin(), line_.end(), r)); }
     void grant(const Request* r) {
-        line_.pop_front();
+        leave(r);
         free_ -= r->n;
     }
 
     mutable std::mutex m_;
     std::condition_variable cv_;
-    std::deque<const Request*> line_;  // requests that wait, the first to be served in front
+    std::deque<const Request*> line_;  // requests that wait, the oldest in front
+    std::chrono::microseconds patience_{};
     int capacity_ = 0, free_ = 0;
 };
 
@@ -128,11 +138,10 @@ struct TeamLease {
         if (!slots_) return;
         {
             std::lock_guard<std::mutex> lk(slots_->m_);
-            auto& line = slots_->line_;
             if (held_)
                 slots_->free_ += request_.n;
             else
-                line.erase(std::find(line.begin(), line.end(), &request_));
+                slots_->leave(&request_);
         }
         slots_->cv_.notify_all();
     }
@@ -143,9 +152,10 @@ struct TeamLease {
         s.line_.push_back(&request_);
         slots_ = &s;
         request_.n = s.units(n);
+        request_.since = std::chrono::steady_clock::now();
     }
     TeamSlots* slots_ = nullptr;
-    TeamSlots::Request request_{0};
+    TeamSlots::Request request_{};
     bool held_ = false;
 };
 

@@ -1,4 +1,5 @@
-// Admission of teams: requests in the order in which they came, from one thread that polls and from several that wait.
+// Admission of teams: requests that have waited for their patience in the order in which they came, from one thread that
+// polls and from several that wait.
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -19,7 +20,7 @@ static void check(bool ok, const char* what) {
 }
 
 static void polled() {
-    TeamSlots s(256);
+    TeamSlots s(256, std::chrono::microseconds(0));
     auto a = std::make_unique<TeamLease>(), b = std::make_unique<TeamLease>(), all = std::make_unique<TeamLease>(),
          gone = std::make_unique<TeamLease>(), c = std::make_unique<TeamLease>();
     check(a->try_take(s, 100) && b->try_take(s, 100), "two leases that fit");
@@ -42,6 +43,23 @@ static void polled() {
     }
     check(refused, "more than there are");
     TeamLease again(s, 256);
+}
+
+// A request that has waited less may be passed, one that has waited longer not.
+static void patience() {
+    TeamSlots s(256, std::chrono::milliseconds(200));
+    auto a = std::make_unique<TeamLease>(), all = std::make_unique<TeamLease>(), b = std::make_unique<TeamLease>(),
+         c = std::make_unique<TeamLease>();
+    check(a->try_take(s, 64) && !all->try_take(s, 256), "a request for all waits");
+    check(b->try_take(s, 64), "a small one passes it");
+    std::this_thread::sleep_for(std::chrono::milliseconds(250));
+    check(!c->try_take(s, 64), "none passes it any more");
+    a.reset();
+    check(!c->try_take(s, 64) && !all->try_take(s, 256), "while one is in flight");
+    b.reset();
+    check(!c->try_take(s, 64) && all->try_take(s, 256), "it is served next");
+    all.reset();
+    check(c->try_take(s, 64), "then the one behind it");
 }
 
 // Whatever teams are in flight together, no XCD has more of their members than units.
@@ -68,7 +86,7 @@ static void xcds() {
 }
 
 static void threads() {
-    TeamSlots s(256);
+    TeamSlots s(256, std::chrono::milliseconds(1));
     std::atomic<int> in_use{0};
     std::atomic<bool> stop{false};
     auto worker = [&](int n, bool poll) {
@@ -93,6 +111,7 @@ static void threads() {
 
 int main() {
     polled();
+    patience();
     xcds();
     threads();
     std::puts("ok");

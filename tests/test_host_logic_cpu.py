@@ -23,7 +23,7 @@ def test_a_team_never_has_more_members_than_compute_units(tmp_path):
     run_host(tmp_path, "team_rows")
 
 
-def test_teams_are_admitted_in_the_order_of_their_requests(tmp_path):
+def test_teams_that_have_waited_are_admitted_in_the_order_of_their_requests(tmp_path):
     run_host(tmp_path, "admission")
 
 
