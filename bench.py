@@ -63,6 +63,7 @@ TRAFFIC_SOURCES = ["paper_2502_10872_amd/csrc/spmv.hpp", "paper_2502_10872_amd/c
                    "paper_2502_10872_amd/csrc/devmath.hpp", "paper_2502_10872_amd/csrc/precompute.hip",
                    "paper_2502_10872_amd/csrc/solver.hip", "paper_2502_10872_amd/csrc/internal.hpp",
                    "paper_2502_10872_amd/csrc/team.hpp", "paper_2502_10872_amd/csrc/team_pcg.hpp",
+                   "paper_2502_10872_amd/csrc/team_host.hpp", "paper_2502_10872_amd/csrc/arrivals.hpp",
                    "paper_2502_10872_amd/csrc/hessian.hip"]
 
 

@@ -537,8 +537,8 @@ __global__ __launch_bounds__(kMaxForceThreads) void force_tiles(const ForceDesc*
 // gathers, come from the work-group size.  It is the largest multiple of 256 threads (one wave per
 // SIMD; uneven multiples leave a SIMD short of room for the second work-group) whose two work-groups
 // per CU fit the waves per SIMD that the kernel's VGPR count allows (512 VGPRs per SIMD lane, allocated
-// in granules of 8, at most 8 waves).  Edge kernels (46-86 VGPRs) get 512-1024 threads, triangle kernels
-// 512-768.  (Measured against a fixed 256 threads with two stencils per thread and pass: edge models
+// in granules of 8, at most 8 waves): 1024 threads for the edge plate in float64 (60 VGPRs), 768 in mixed precision (68
+// and 70), 512 for the edge shells (88-100) and the triangle models (105-128).  (Measured against a fixed 256 threads with two stencils per thread and pass: edge models
 // 9-15% faster, float shells 5%, the rest equal or up to 4% faster.)
 template <typename Kernel>
 int force_threads(Kernel kernel) {

@@ -500,8 +500,9 @@ __device__ __forceinline__ bool ms_iteration_state(const double* cst, const doub
 // shuffles, until too few rows share a wave's loads.
 constexpr int kMsLanesF64 = 8;
 constexpr int kMsLanesF32 = 4;
-// The staged product (below) from this many rows up; on smaller meshes its latency floor exceeds the CSR
-// product's.  Measured with 512-row groups on SS cylinders, staged against CSR product, FP64: 10.1 / 5.3 us
+// The staged product (below) from this many rows up where the mesh has no team layout; with one its chain, which then
+// only follows a team that gave up or a request for it, is staged at every size (the tangent has one layout).  On
+// smaller meshes the staged product's latency floor exceeds the CSR product's.  Measured with 512-row groups on SS cylinders, staged against CSR product, FP64: 10.1 / 5.3 us
 // at 4K rows, 14.4 / 10.2 at 33K, 15.0 / 14.1 at 48K, 15.5 / 18.1 at 65K, 20.2 / 32.9 at 131K, 144 / 317 at
 // 1M.  With the smaller groups of mid-size meshes (ms_group_rows), whole steps, staged against CSR, FP64 and
 // mixed: 12.0 / 10.3 and 11.3 / 10.4 ms at 16K rows, 9.9 / 10.9 and 10.0 / 9.4 at 33K, 12.5 / 14.4 and
@@ -728,7 +729,8 @@ __global__ __launch_bounds__(kMsBlk) void ms_iter_update(const double* __restric
     ms_partials<2>(v, part, ngroups);
 }
 
-// Small meshes (at most kMsSmallRows vertices): the whole PCG iteration in one work-group, up to `count`
+// Small meshes (at most kMsSmallRows vertices) in the CSR layout (the direct product's; otherwise they are teams of one
+// member): the whole PCG iteration in one work-group, up to `count`
 // iterations per launch, work-group barriers in place of the kernel boundaries of the chain above (whose
 // launches, some microseconds each, dominate at these sizes).  The direction p and the product q live in
 // LDS for the launch (p is read from and written back to m.p at its ends); LANES lanes share a row's

@@ -1024,7 +1024,7 @@ shell_status_t batch_step(shell_batch_s& b, const shell_step_params_t* p, int np
     return step_impl<double, double>(b, p, nparams, stats, s, qs);
 }
 
-// test hook: the ticks (10 ns) a team's wait of this simulation's own steps may take
+// test hook, not declared in shell.h: the ticks (10 ns) a team's wait of this simulation's own steps may take
 extern "C" void shell_test_team_wait(shell_sim_s* sim, uint64_t ticks) {
     if (sim && sim->solo) sim->solo->team_wait = ticks;
     if (sim && sim->ms) sim->ms->team_wait = ticks;

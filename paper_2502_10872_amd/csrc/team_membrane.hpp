@@ -51,16 +51,20 @@ __host__ __device__ constexpr size_t team_membrane_lds(int rows, int halo) {
 }
 
 // Pairs of K_s and blocks requested together (see kTeamBatch): as many as the registers beside the rows'
-// vectors hold.
+// vectors hold.  Registers by rows per thread, FP64 / mixed: 1 106 / 136, 2 132 / 160, 4 171 / 196, 6 195 / 218, 8 238 /
+// 256, where the mixed instance spills two (12 bytes of scratch per lane); those of one and two rows hold 20 bytes of
+// scratch, for scalar values, and no vector register.
 template <typename VT>
 constexpr int kMsTeamPairs = sizeof(VT) == 8 ? 3 : 9;
 template <typename VT, int RPL>
 constexpr int kMsTeamBlocks = sizeof(VT) == 8 ? (RPL <= 4 ? 2 : 1) : (RPL <= 4 ? 4 : 2);
 
-// Matrices that outgrow the 256 MB last-level cache (from 262144 rows in float64, 524288 in float32) are read with
-// non-temporal loads, which keep the halo's exchange and the little that is read again in the caches:
-// 1M rows 144 -> 122 us per iteration FP64 and 87 -> 73 mixed, 524K rows FP64 74 -> 64.  Smaller ones are read
-// again from the caches with plain loads (16384 rows: 10.4 us FP64 against 12.1 non-temporal).
+// Matrices that outgrow the 256 MB last-level cache are read with non-temporal loads, which keep the halo's exchange and
+// the little that is read again in the caches: 1M rows 144 -> 122 us per iteration FP64 and 87 -> 73 mixed, 524K
+// rows FP64 74 -> 64.  Smaller ones are read again from the caches with plain loads (16384 rows: 10.4 us FP64 against
+// 12.1 non-temporal).  The line is drawn by rows per thread, a constant of the instance: a smoothed or FVM mesh's
+// matrices pass 256 MiB at some 380,000 rows FP64 and 700,000 mixed, and the instances change at 262144 and
+// 524288, just below; an edge mesh's, of fewer entries per row, at some 420,000 and 790,000.
 template <typename VT, int RPL>
 constexpr bool kMsTeamStream = sizeof(VT) == 8 ? RPL > 2 : RPL > 4;
 template <bool STREAM, typename V>

@@ -1,15 +1,19 @@
 // The three-column Jacobi PCG of the bending step as one kernel per solve (see team.hpp for how its
 // work-groups meet).  Included once, by solver.hip, after pcg_kernels.hpp.
 //
+// z = D^-1 r takes the reciprocal of the diagonal from inv_fast (an estimate and two Newton steps, the last bit or two
+// off), where the chain reads a stored, correctly rounded 1 / d: the preconditioner alone differs, and the two
+// solves by rounding.
+//
 // A member owns d.trows consecutive rows: row base + s T + thread is the thread's s-th.  r, y, q and the row's
 // diagonal stay in registers from the first iteration to the last; the directions p of the own rows and
 // of the halo columns (the columns of other members' rows) in LDS, where every member advances its own
 // copy, p = z + beta p, from the same z bits.  Per iteration a member therefore streams only its rows'
 // off-diagonal entries, and exchanges the z of the rows that other members read and nine sums.
 //
-// What bounds it.  Up to some 100,000 rows latency: two meetings (about 2 us each with nine members, 3.5 us with 128), the
-// halo's round trip through memory and a row's chain of LDS reads; 8.5 us per iteration at 4225 rows, 11.5 at
-// 65536.  At a million rows the matrix stream: 239 MB of float64 pairs in 32 us (7.4 TB/s, part of it from the
+// What bounds it.  Up to some 100,000 rows latency: two meetings (about 2 us each with 9 to 17 members, 3.5 us with 128), the
+// halo's round trip through memory and a row's chain of LDS reads; 7.6 us per iteration at 4225 rows (17 members),
+// 11.5 at 65536.  At a million rows the matrix stream: 239 MB of float64 pairs in 32 us (7.4 TB/s, part of it from the
 // last-level cache), 126 MB of float32 pairs in 22.5 us, of 42 and 31 us per iteration; the chain's two kernels
 // moved 483 and 301 MB in 107 and 71.  Measured at 1M rows and not kept: 1024 threads with 128 registers (y in
 // memory or scratch: 50 and 35 us), the next batch of entries requested while one is multiplied (48 and 42 us: the
